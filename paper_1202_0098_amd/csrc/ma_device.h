@@ -29,7 +29,7 @@
 //   k_basis_m  the columns of one atom in lockstep, every SpMV an SpMM.
 // All write the pair and the basis rows the outputs need into a chunk buffer.
 //
-// Eigensolver kernel (one wavefront per column): Cholesky of S~, Householder
+// Eigensolver kernel (ma_eig.hip): Cholesky of S~, Householder
 // tridiagonalisation and implicit QL of L^-1 H~ L^-T, the Ritz vectors at
 // the rows of the outputs, Ritz values and weights, and either the
 // amplitudes v_ia v_ja (chemical potential still to be found) or the
@@ -2301,405 +2301,6 @@ __global__ void __launch_bounds__(NT) k_basis_s(DevSystem S, DevJob J)
         basis_small<O, NT, NU, PREC>(S, J, Ub, xa, xb, xz, scratch, rs, cf, srp, sblk, red, redf,
                                      c, s);
     });
-}
-
-// ------------------------------------------------------------------------
-// reduced generalised eigenproblems and column outputs (a6, a7)
-// ------------------------------------------------------------------------
-// One wavefront per column of the chunk, everything in LDS:
-//   1/2 (X + X^T) -> H~, S~; Cholesky S~ = Lc Lc^T (right-looking);
-//   A = Lc^-1 H~ Lc^-T (two right-looking triangular solves, a lane per column);
-//   Householder reduction A = Q T Q^T to tridiagonal T, Q accumulated backwards;
-//   implicit QL iterations with shifts on T (the published QL algorithm for
-//   symmetric tridiagonal matrices: Bowdler, Martin, Reinsch and Wilkinson,
-//   Numer. Math. 11 (1968)), each plane rotation applied to the rows of Z = Q
-//   by one lane per row;
-//   C = Lc^-T Z.
-// Every lane runs the scalar recurrences of the QL sweeps redundantly, so they
-// need no broadcasts.  Then v_a at row j, (S v_a)_j, the Ritz values in
-// ascending order and the weights w_a = v_ja (S v_a)_j; then either the
-// amplitudes v_ia v_ja at the pattern rows or, with a given chemical
-// potential, rho_ij, pi_ij (Eqs. 13-14) and E_j, N_j (Eq. 17).
-template <typename TA>
-__global__ void __launch_bounds__(64) k_eig(DevSystem S, DevJob J)
-{
-    extern __shared__ double smem[];
-    const int nu = J.nu;
-    // Two nu x nu matrices in LDS (A, and Z column-major); the Cholesky
-    // factor of S~ lives in the Z area until Z is needed, waits in the S~
-    // slot of the chunk buffer meanwhile, and comes back for C = Lc^-T Z.
-    double *A = smem, *Z = smem + nu * nu, *B = Z;
-    double *ev = smem + 2 * nu * nu, *vj = ev + nu, *svj = vj + nu, *fw = svj + nu;
-    double *hh = fw + nu, *ee = hh + nu, *rd = ee + nu;
-    double *upj = rd + nu;   // 2 nu
-    int *rank = reinterpret_cast<int *>(upj + 2 * nu);
-    int *inv = rank + nu;
-    __shared__ double hv[kMaxNu];   // current Householder vector (separate objects: the
-    __shared__ double hq[kMaxNu];   // compiler may keep their loads ahead of A's stores)
-    const int lane = threadIdx.x;
-    const int o = S.o;
-    for (int s = blockIdx.x; s < J.cn; s += gridDim.x) {
-        const int c = J.order[J.c0 + s];
-        double *mid = J.mid + (int64_t)s * J.mid_stride;
-        const double *Up = mid + 2 * (int64_t)nu * nu;
-        int32_t *st = J.stats + (int64_t)c * kStats;
-        int L = st[3] == 0 ? st[0] : 0;
-        int status = 0;
-#pragma unroll 4
-        for (int e = lane; e < L * L; e += 64) {
-            const int i = e / L, k = e - i * L;
-            A[e] = 0.5 * (mid[i * nu + k] + mid[k * nu + i]);
-            B[e] = 0.5 * (mid[nu * nu + i * nu + k] + mid[nu * nu + k * nu + i]);
-        }
-        // basis rows at j: u_m[j] and (S u_m)[j]
-        for (int m = lane; m < L; m += 64) {
-            upj[m] = Up[m];
-            upj[nu + m] = Up[nu + m];
-        }
-        __syncthreads();
-
-        // Cholesky S~ = Lc Lc^T in the lower triangle of B
-        for (int k = 0; k < L; ++k) {
-            double dk = B[k * L + k];
-            if (!(dk > 0.0)) {
-                status = -4;
-                dk = 1.0;
-            }
-            const double lk = sqrt(dk), rl = 1.0 / lk;
-            for (int i = k + 1 + lane; i < L; i += 64) B[i * L + k] *= rl;
-            __syncthreads();
-            for (int j = k + 1 + lane; j < L; j += 64) {
-                const double bjk = B[j * L + k];
-                #pragma unroll 4
-                for (int i = j; i < L; ++i) B[i * L + j] -= B[i * L + k] * bjk;
-            }
-            if (lane == 0) {
-                B[k * L + k] = lk;
-                rd[k] = rl;
-            }
-            __syncthreads();
-        }
-        // A = Lc^-1 H~ Lc^-T in place: W = Lc^-1 A (a lane per column), then
-        // A = Lc^-1 W^T
-        for (int pass = 0; pass < 2; ++pass) {
-            for (int k = 0; k < L; ++k)
-                for (int cc = lane; cc < L; cc += 64) {
-                    const double ak = A[k * L + cc] * rd[k];
-                    A[k * L + cc] = ak;
-                    #pragma unroll 4
-                    for (int i = k + 1; i < L; ++i) A[i * L + cc] -= B[i * L + k] * ak;
-                }
-            __syncthreads();
-            if (pass == 0) {
-                for (int e = lane; e < L * L; e += 64) {
-                    const int i = e / L, k = e - i * L;
-                    if (i < k) {
-                        const double x = A[i * L + k];
-                        A[i * L + k] = A[k * L + i];
-                        A[k * L + i] = x;
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        // the factor waits in the S~ slot of the chunk buffer (read above,
-        // not read again) while Z takes its place
-        for (int e = lane; e < L * L; e += 64) mid[nu * nu + e] = B[e];
-        __syncthreads();
-        for (int e = lane; e < L * L; e += 64) {
-            const int i = e / L, k = e - i * L;
-            if (i < k) {
-                const double v = 0.5 * (A[i * L + k] + A[k * L + i]);
-                A[i * L + k] = v;
-                A[k * L + i] = v;
-            }
-        }
-        __syncthreads();
-
-        // Householder reduction to tridiagonal form.  Step k reflects
-        // x = A[k+1.., k] onto alpha e_1 with P = I - v v^T / h,
-        // v = x - alpha e_1, h = |v|^2 / 2; v stays in column k below the
-        // diagonal, h in hh[k], alpha is the sub-diagonal ee[k].
-        for (int k = 0; k + 2 < L; ++k) {
-            const int i = k + 1 + lane;
-            const double xi = i < L ? A[i * L + k] : 0.0;
-            const double sig = wave_sum(xi * xi);
-            const double x0 = A[(k + 1) * L + k];
-            double alpha = x0, h = 0.0;
-            if (sig > 0.0) {
-                alpha = x0 >= 0.0 ? -sqrt(sig) : sqrt(sig);
-                h = sig - x0 * alpha;
-            }
-            if (lane == 0) {
-                ee[k] = alpha;
-                hh[k] = h;
-            }
-            if (h > 0.0) {
-                // v = x - alpha e_1, kept in column k and in hv
-                const double vi = (i == k + 1) ? x0 - alpha : xi;
-                if (i < L) {
-                    hv[i] = vi;
-                    A[i * L + k] = vi;
-                }
-                __syncthreads();
-                // p = A' v / h, K = v^T p / (2 h), q = p - K v (a lane per column j)
-                const int j = k + 1 + lane;
-                double pj = 0.0, vjj = 0.0;
-                if (j < L) {
-                    #pragma unroll 4
-                    for (int ii = k + 1; ii < L; ++ii) pj += A[ii * L + j] * hv[ii];
-                    pj /= h;
-                    vjj = hv[j];
-                }
-                const double K = wave_sum(vjj * pj) / (2.0 * h);
-                const double qj = pj - K * vjj;
-                if (j < L) hq[j] = qj;
-                __syncthreads();
-                // A' -= v q^T + q v^T
-                if (j < L)
-                    #pragma unroll 4
-                    for (int ii = k + 1; ii < L; ++ii)
-                        A[ii * L + j] -= hv[ii] * qj + hq[ii] * vjj;
-            }
-            __syncthreads();
-        }
-        for (int i = lane; i < L; i += 64) ev[i] = A[i * L + i];
-        if (lane == 0 && L >= 2) ee[L - 2] = A[(L - 1) * L + L - 2];
-        if (lane == 0 && L >= 1) ee[L - 1] = 0.0;
-        // Z = P_0 P_1 ... P_{L-3} (column-major), accumulated from the last
-        // reflector; P_k leaves columns 0..k unchanged
-        for (int e = lane; e < L * L; e += 64) Z[e] = (e / L == e % L) ? 1.0 : 0.0;
-        __syncthreads();
-        for (int k = L - 3; k >= 0; --k) {
-            const double h = hh[k];
-            if (!(h > 0.0)) continue;
-            for (int cc = k + 1 + lane; cc < L; cc += 64) {
-                double t = 0.0;
-                #pragma unroll 4
-                for (int i = k + 1; i < L; ++i) t += A[i * L + k] * Z[cc * L + i];
-                t /= h;
-                #pragma unroll 4
-                for (int i = k + 1; i < L; ++i) Z[cc * L + i] -= A[i * L + k] * t;
-            }
-        }
-        __syncthreads();
-
-        // Implicit QL sweeps on (ev, ee).  For the leading unreduced block
-        // [l, m] (ee[m] negligible against its diagonal neighbours), a shift
-        // from the 2 x 2 at l, then plane rotations chasing the bulge from m
-        // up to l.  At most 64 sweeps per eigenvalue.  The rotation loop is
-        // software-pipelined: the entries of the next rotation are loaded one
-        // rotation ahead, and the rotated column i stays in a register for the
-        // next rotation (columns i + 1 are final once written).
-        for (int l = 0; l < L && status == 0; ++l) {
-            int sweeps = 0;
-            for (;;) {
-                // m: the first k >= l with ee[k] negligible (L - 1 if none),
-                // one lane per k
-                bool small = lane == L - 1;
-                if (lane >= l && lane < L - 1)
-                    small = fabs(ee[lane]) <= DBL_EPSILON * (fabs(ev[lane]) + fabs(ev[lane + 1]));
-                const unsigned long long msk =
-                    __ballot(small) & ~((l > 0 ? (1ull << l) : 1ull) - 1ull);
-                const int m = __ffsll((long long)msk) - 1;
-                if (m == l) break;
-                if (++sweeps > 64) {
-                    status = -5;
-                    break;
-                }
-                const double el = ee[l], dl0 = ev[l], dl1 = ev[l + 1], dm = ev[m];
-                const double t0 = (dl1 - dl0) / (2.0 * el);
-                const double r0 = sqrt(t0 * t0 + 1.0);
-                double g = dm - dl0 + el / (t0 + (t0 >= 0.0 ? r0 : -r0));
-                double sn = 1.0, cs = 1.0, p = 0.0;
-                bool underflow = false;
-                const bool row = lane < L;
-                double e_i = ee[m - 1], d_i = ev[m - 1], d_i1 = dm;
-                double z_i1 = row ? Z[m * L + lane] : 0.0;
-                double z_i = row ? Z[(m - 1) * L + lane] : 0.0;
-                for (int i = m - 1; i >= l; --i) {
-                    double e_n = 0.0, d_n = 0.0, z_n = 0.0;
-                    if (i > l) {
-                        e_n = ee[i - 1];
-                        d_n = ev[i - 1];
-                        z_n = row ? Z[(i - 1) * L + lane] : 0.0;
-                    }
-                    const double f = sn * e_i, b = cs * e_i;
-                    const double r2 = f * f + g * g;
-                    if (r2 == 0.0) {
-                        const double dnew = d_i1 - p;
-                        if (lane == 0) {
-                            ee[i + 1] = 0.0;
-                            ev[i + 1] = dnew;
-                            ee[m] = 0.0;
-                        }
-                        if (row) Z[(i + 1) * L + lane] = z_i1;
-                        underflow = true;
-                        break;
-                    }
-                    const double ir = rsqrt(r2);
-                    sn = f * ir;
-                    cs = g * ir;
-                    g = d_i1 - p;
-                    const double rr = (d_i - g) * sn + 2.0 * cs * b;
-                    p = sn * rr;
-                    if (lane == 0) {
-                        ee[i + 1] = r2 * ir;
-                        ev[i + 1] = g + p;
-                    }
-                    g = cs * rr - b;
-                    const double zn1 = sn * z_i + cs * z_i1;
-                    const double zn0 = cs * z_i - sn * z_i1;
-                    if (row) Z[(i + 1) * L + lane] = zn1;
-                    z_i1 = zn0;
-                    z_i = z_n;
-                    e_i = e_n;
-                    d_i1 = d_i;
-                    d_i = d_n;
-                }
-                if (underflow) continue;
-                if (row) Z[l * L + lane] = z_i1;
-                if (lane == 0) {
-                    ev[l] = dl0 - p;
-                    ee[l] = g;
-                    ee[m] = 0.0;
-                }
-            }
-        }
-        __syncthreads();
-        // ascending ranks of the eigenvalues
-        for (int a = lane; a < L; a += 64) {
-            int rk = 0;
-            const double va = ev[a];
-            #pragma unroll 4
-            for (int bb = 0; bb < L; ++bb)
-                if (ev[bb] < va || (ev[bb] == va && bb < a)) ++rk;
-            rank[a] = rk;
-        }
-        // C = Lc^-T Z -> A (row-major), a lane per column; the factor back
-        // in the Z area once Z is copied
-        for (int a = lane; a < L; a += 64) {
-            #pragma unroll 4
-            for (int i = 0; i < L; ++i) A[i * L + a] = Z[a * L + i];
-        }
-        __syncthreads();
-        for (int e = lane; e < L * L; e += 64) B[e] = mid[nu * nu + e];
-        __syncthreads();
-        for (int a = lane; a < L; a += 64) {
-            for (int k = L - 1; k >= 0; --k) {
-                const double ck = A[k * L + a] * rd[k];
-                A[k * L + a] = ck;
-                #pragma unroll 4
-                for (int i = 0; i < k; ++i) A[i * L + a] -= B[k * L + i] * ck;
-            }
-        }
-        __syncthreads();
-        if (status != 0) {
-            L = 0;
-            if (lane == 0) {
-                st[0] = 0;
-                st[3] = status;
-                atomicMin(J.fail, c);
-            }
-        }
-        const double *C = A;
-        // v_a and (S v_a) at row j (a lane per Ritz vector; the basis rows
-        // are read at the same address by every lane)
-        for (int a = lane; a < L; a += 64) {
-            double v1 = 0.0, v2 = 0.0;
-            #pragma unroll 4
-            for (int m = 0; m < L; ++m) {
-                const double cma = C[m * L + a];
-                v1 += upj[m] * cma;
-                v2 += upj[nu + m] * cma;
-            }
-            vj[a] = v1;
-            svj[a] = v2;
-        }
-        __syncthreads();
-        double *eps_o = J.eps + (int64_t)c * nu, *wts_o = J.wts + (int64_t)c * nu;
-        for (int a = lane; a < nu; a += 64) {
-            if (a < L) {
-                eps_o[rank[a]] = ev[a];
-                wts_o[rank[a]] = vj[a] * svj[a];
-                inv[rank[a]] = a;
-            } else {
-                eps_o[a] = NAN;
-                wts_o[a] = 0.0;
-            }
-        }
-        const int j = J.cols[c];
-        const int At = j / o, r = j - At * o;
-        const int64_t kb0 = S.blk_ptr[At];
-        const int npat = (int)(S.blk_ptr[At + 1] - kb0) * o;
-        if (!J.direct) {
-            // V at the pattern rows on the FP64 matrix cores: 16 x 16 tiles of
-            // (basis rows of the chunk buffer, npat x L) x (C, L x L, LDS), with
-            // v_mfma_f64_16x16x4f64: lane l feeds A[l%16][l/16], B[l/16][l%16]
-            // and receives D[4 j + l/16][l%16]
-            TA *amp = reinterpret_cast<TA *>(J.amp) + J.amp_off[c];
-            const int nrt = (npat + 15) >> 4, nct = (nu + 15) >> 4;
-            const int kq = lane >> 4, l16 = lane & 15;
-            for (int mt = 0; mt < nrt; ++mt) {
-                const int arow = mt * 16 + l16;
-                // this lane's basis-row operands for the first 32 k, loaded together
-                double avs[8];
-#pragma unroll
-                for (int st4 = 0; st4 < 8; ++st4) {
-                    const int kk = 4 * st4 + kq;
-                    avs[st4] = (arow < npat && kk < L) ? Up[(2 + arow) * nu + kk] : 0.0;
-                }
-              for (int ct = 0; ct < nct; ++ct) {
-                const int bcol = ct * 16 + l16;
-                dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-                for (int k0 = 0; k0 < L; k0 += 4) {
-                    const int kk = k0 + kq;
-                    const double av = k0 < 32 ? avs[(k0 >> 2) & 7]
-                                      : (arow < npat && kk < L) ? Up[(2 + arow) * nu + kk] : 0.0;
-                    const double bv = (bcol < L && kk < L) ? C[kk * L + bcol] : 0.0;
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int tr = mt * 16 + 4 * jj + kq;
-                    if (tr < npat && bcol < nu) {
-                        if (bcol < L) amp[tr * nu + rank[bcol]] = (TA)(acc[jj] * vj[bcol]);
-                        else amp[tr * nu + bcol] = (TA)0.0;
-                    }
-                }
-              }
-            }
-        } else {
-            __syncthreads();
-            for (int k = lane; k < L; k += 64) fw[k] = fermi((ev[inv[k]] - J.mu) / J.kT);
-            __syncthreads();
-            double ep = 0.0, np_ = 0.0;
-            for (int tt = lane; tt < npat; tt += 64) {
-                double sr = 0.0, sp = 0.0;
-                for (int k = 0; k < L; ++k) {
-                    const int a = inv[k];
-                    double v = 0.0;
-                    #pragma unroll 4
-                    for (int m = 0; m < L; ++m) v += Up[(2 + tt) * nu + m] * C[m * L + a];
-                    const double am = v * vj[a];
-                    sr += fw[k] * am;
-                    sp += (fw[k] * ev[a]) * am;
-                }
-                const int64_t slot = ((kb0 + tt / o) * o + r) * o + (tt % o);
-                if (J.rho) J.rho[slot] = sr;
-                if (J.pi) J.pi[slot] = sp;
-                ep += sr * S.Hd[slot];
-                np_ += sr * S.Sd[slot];
-            }
-            ep = wave_sum(ep);
-            np_ = wave_sum(np_);
-            if (lane == 0) {
-                J.Ecol[c] = ep;
-                J.Ncol[c] = np_;
-            }
-        }
-        __syncthreads();   // LDS is reused by the next column
-    }
 }
 
 __global__ void k_reset(int *queue, int *fail, int reset_fail)

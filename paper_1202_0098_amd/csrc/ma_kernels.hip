@@ -179,16 +179,6 @@ hipError_t basis_occupancy(const DevSystem &S, const DevJob &J, int kind, int *b
                         NTG, smem, bpc);
 }
 
-hipError_t launch_eig(const DevSystem &S, const DevJob &J, hipStream_t st)
-{
-    const size_t smem = sizeof(double) * (2 * (size_t)J.nu * J.nu + 10 * (size_t)J.nu) +
-                        sizeof(int) * 2 * (size_t)J.nu;
-    const int grid = J.cn < (1 << 20) ? J.cn : (1 << 20);
-    if (grid < 1) return hipSuccess;
-    if (J.precision == 0) return launch_with_smem(k_eig<double>, grid, 64, smem, st, S, J);
-    return launch_with_smem(k_eig<float>, grid, 64, smem, st, S, J);
-}
-
 // grid of the bracket and count kernels: about 2,048 Ritz pairs per
 // workgroup, between 64 and kCountBlocks workgroups
 int count_grid(int ncols, int nu)
