@@ -131,7 +131,9 @@ typedef struct {
     int32_t use_graph;      /* 1: capture the launch sequence in a hipGraph and replay it
                                while the configuration and buffers are unchanged */
     int32_t basis_kernel;   /* MA_BASIS_AUTO: the autotuned kernel for (p, q, precision)
-                               if ma_autotune ran, else MA_BASIS_WORKSPACE.
+                               if ma_autotune ran, else MA_BASIS_ONCHIP in its register
+                               form (MA_PREC_FP64, o = 4, regions of at most 512
+                               orbitals, p + q <= 32), else MA_BASIS_WORKSPACE.
                                MA_BASIS_WORKSPACE: one column per workgroup, basis in a
                                device workspace, one dot sweep and one update sweep per
                                basis vector.
@@ -157,7 +159,8 @@ typedef struct {
                                stream beside the later basis kernels, with a ring of
                                chunk buffers of at most 8 GiB; 0 or 1: off (chunks in
                                sequence on one stream); -1 (default): the autotuned
-                               choice for (p, q, precision) if ma_autotune ran, else 4 */
+                               choice for (p, q, precision) if ma_autotune ran, else 4
+                               (0 where the automatic kernel is MA_BASIS_ONCHIP) */
     int32_t keep_sj;        /* 1: keep each solved column's s_j = S_A^-1 e_j (region
                                vector, FP64, M * nmax doubles in all) for a later solve
                                with MA_START_PREVIOUS; the kept set belongs to the

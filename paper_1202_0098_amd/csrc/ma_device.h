@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "ma_internal.h"
+#include "ma_lanes.h"
 
 namespace ma {
 

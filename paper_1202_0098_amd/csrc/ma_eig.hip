@@ -1,6 +1,6 @@
 // Reduced generalised eigenproblems and column outputs (a6, a7), and the
 // launcher of the kernel.
-#include "ma_lanes.h"
+#include "ma_device.h"
 
 namespace ma {
 

@@ -1019,8 +1019,6 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     const ma_ctx::Tune *tn = ctx->find_tune(p, q, opts.precision);
     P.sched = sched_override >= 0 ? sched_override
               : opts.schedule >= 0 ? opts.schedule : (tn ? tn->sched : MA_SCHED_LPT);
-    const int pipe = opts.pipeline >= 0 ? opts.pipeline : (tn && tn->pipe >= 0 ? tn->pipe : 4);
-
     ma::DevSystem &S = P.S;
     ma::DevJob &J = P.J;
     S = ctx->dev_system();
@@ -1051,11 +1049,21 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         return ctx->fail(MA_EINVAL, "the atom basis kernel needs 4 or 9 orbitals per atom, an "
                          "FP64-vector precision mode and regions it can stage (o = %d, %d "
                          "orbitals, precision %d)", ctx->o, ctx->nmax, opts.precision);
-    // automatic choice: the autotuned kernel if there is one, else the
-    // workspace kernel (the fastest untuned choice on every shape measured)
+    // Automatic choice: the autotuned kernel if there is one, else the on-chip
+    // kernel's resident form where it holds the shape (4,000 columns of 480
+    // orbitals, nu = 30: basis 3.1 ms against 4.5), else the workspace kernel.
+    // On-chip means the resident form wherever that holds the shape.
     int want_kernel = opts.basis_kernel;
-    if (want_kernel == MA_BASIS_AUTO)
-        want_kernel = tn && tn->kernel != MA_BASIS_AUTO ? tn->kernel : MA_BASIS_WORKSPACE;
+    if (want_kernel == MA_BASIS_AUTO && tn) want_kernel = tn->kernel;
+    const bool resident = (want_kernel == MA_BASIS_AUTO || (want_kernel == MA_BASIS_ONCHIP && fits)) &&
+                          ma::basis_resident_fits(ctx->nmax, P.nu, q, ctx->o, opts.precision,
+                                                  ma::lidx_bytes(ctx->max_nat, (int)ctx->max_lnnz));
+    if (want_kernel == MA_BASIS_AUTO) want_kernel = MA_BASIS_WORKSPACE;
+    // The resident kernel's workgroups take every register of their compute
+    // unit, so that no eigensolver runs beside them: chunks in sequence (4,096
+    // sp3 atoms 16.8 ms, pipelined 17.3 ms).
+    const int pipe = opts.pipeline >= 0 ? opts.pipeline
+                     : tn && tn->pipe >= 0 ? tn->pipe : resident ? 0 : 4;
     // the group kernel neither starts from nor keeps whole-region s_j
     const bool sj_io = opts.start == MA_START_PREVIOUS || opts.keep_sj;
     if (opts.basis_kernel == MA_BASIS_GROUP && sj_io)
@@ -1063,17 +1071,19 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     if ((want_kernel == MA_BASIS_ONCHIP && !fits) || (want_kernel == MA_BASIS_GROUP && !gfits) ||
         (want_kernel == MA_BASIS_ATOM && !afits) || (want_kernel == MA_BASIS_GROUP && sj_io))
         want_kernel = MA_BASIS_WORKSPACE;
-    P.kind = want_kernel == MA_BASIS_ONCHIP ? ma::kBasisOnchip
+    P.kind = resident ? ma::kBasisResident
+             : want_kernel == MA_BASIS_ONCHIP ? ma::kBasisOnchip
              : want_kernel == MA_BASIS_GROUP ? ma::kBasisGroup
              : want_kernel == MA_BASIS_ATOM ? ma::kBasisAtom : ma::kBasisWorkspace;
     const int o = ctx->o;
-    J.lidx = P.kind == ma::kBasisWorkspace ? S.lidx
+    J.lidx = P.kind == ma::kBasisResident ? 1
+             : P.kind == ma::kBasisWorkspace ? S.lidx
              : P.kind == ma::kBasisOnchip
                  ? (ma::onchip_lidx_fits(ctx->nmax, P.nu, ctx->max_nat, (int)ctx->max_lnnz) ? 1 : 0)
              : P.kind == ma::kBasisAtom
                  ? (ma::atom_lidx_fits(ctx->nmax, o, ctx->max_nat, (int)ctx->max_lnnz) ? 1 : 0)
                  : 0;
-    J.ws_stride = P.kind == ma::kBasisOnchip ? 0
+    J.ws_stride = P.kind == ma::kBasisOnchip || P.kind == ma::kBasisResident ? 0
                   : P.kind == ma::kBasisAtom ? ma::atom_ws_doubles(o, P.nu, q, ctx->nmax)
                   : (int64_t)(P.kind == ma::kBasisGroup ? ma::basis_group_width(o) : 1) *
                         (3 * P.nu + q) * ctx->nmax;
@@ -1257,7 +1267,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
                  n_partial = sizeof(double) * (ma::kCountBlocks * ma::kBisectTrials + 1),
                  n_E = sizeof(double) * ncols, n_sums = sizeof(double) * 2,
                  n_mid = sizeof(double) * (size_t)J.mid_stride * P.max_cn * P.nbuf,
-                 slot_bytes = P.kind == ma::kBasisOnchip ? 0 : sizeof(double) * (size_t)J.ws_stride;
+                 slot_bytes = sizeof(double) * (size_t)J.ws_stride;
     void *b_cols, *b_order, *b_qb, *b_gstart, *b_ws = nullptr, *b_mid, *b_eps = nullptr,
          *b_wts = nullptr, *b_amp = nullptr, *b_aoff = nullptr, *b_stats = nullptr,
          *b_feat = nullptr, *b_x0 = nullptr, *b_x0full = nullptr, *b_ctl, *b_lohi, *b_partial,
@@ -1396,7 +1406,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     P.ctl = static_cast<int *>(b_ctl);
     J.queue = P.ctl;
     J.fail = P.ctl + ma::kMaxQueues;
-    J.ws = P.kind == ma::kBasisOnchip ? nullptr : static_cast<double *>(b_ws);
+    J.ws = static_cast<double *>(b_ws);
     J.mid = static_cast<double *>(b_mid);
     J.eps = eps ? eps : static_cast<double *>(b_eps);
     J.wts = wts ? wts : static_cast<double *>(b_wts);

@@ -113,10 +113,12 @@ constexpr int kStats = 8;      // nu_eff, CG iterations, FP64 residual evaluatio
 // workgroup, U in LDS and S U, chain in registers (regions of at most
 // kSmallRows orbitals, nu <= 32, q <= nu_cap / 2).  Atom-group kernel: the
 // requested columns of one atom in lockstep (o = 4 or 9), one SpMM per step
-// for all of them, bases in the workspace.
+// for all of them, bases in the workspace.  Resident kernel: one column per
+// workgroup, the basis in the workgroup's registers (FP64, o = 4; index_bytes:
+// the LDS of a staged region index).
 constexpr int kMaxQueues = 8;
 constexpr int kSmallRows = 512;
-enum { kBasisWorkspace = 0, kBasisOnchip = 1, kBasisGroup = 2, kBasisAtom = 3 };
+enum { kBasisWorkspace = 0, kBasisOnchip = 1, kBasisGroup = 2, kBasisAtom = 3, kBasisResident = 4 };
 bool basis_small_fits(int nmax, int nu, int q, int o);
 bool basis_group_fits(int nmax, int nu, int o);
 // Atom kernel: the o columns of one atom in lockstep, every operator pass an
@@ -125,6 +127,9 @@ bool basis_atom_fits(int nmax, int nu, int o, int precision);
 bool atom_lidx_fits(int nmax, int o, int max_nat, int max_lnnz);
 __host__ __device__ int64_t atom_slice_doubles(int nu, int q, int64_t ld);
 __host__ __device__ int64_t atom_ws_doubles(int o, int nu, int q, int64_t ld);
+bool basis_resident_fits(int nmax, int nu, int q, int o, int precision, size_t index_bytes);
+void *basis_r_kernel(int o, int nmax, int nu, int q, size_t index_bytes, int *threads, size_t *smem);
+size_t lidx_bytes(int max_nat, int max_lnnz);
 int basis_group_width(int o);   // columns of one atom solved together
 size_t basis_smem_bytes(int nmax, int nu, int kind, int o);
 // whether the workspace (resp. on-chip) kernel keeps a region's local block

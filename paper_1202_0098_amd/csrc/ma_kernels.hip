@@ -142,6 +142,14 @@ hipError_t launch_reset(int *queue, int *fail, int reset_fail, hipStream_t st)
 
 hipError_t launch_basis(const DevSystem &S, const DevJob &J, int kind, int slots, hipStream_t st)
 {
+    if (kind == kBasisResident) {
+        int nt = 0;
+        size_t lds = 0;
+        basis_fn k = (basis_fn)basis_r_kernel(S.o, S.nmax, J.nu, J.q, lidx_bytes(S.max_nat, S.max_lnnz),
+                                              &nt, &lds);
+        if (!k) return hipErrorInvalidConfiguration;
+        return launch_with_smem(k, slots, nt, lds, st, S, J);
+    }
     const size_t smem = basis_smem_bytes(S.nmax, J.nu, kind, S.o) +
                         (J.lidx ? lidx_bytes(S.max_nat, S.max_lnnz) : 0);
     if (kind == kBasisOnchip) {
@@ -163,6 +171,14 @@ hipError_t launch_basis(const DevSystem &S, const DevJob &J, int kind, int slots
 
 hipError_t basis_occupancy(const DevSystem &S, const DevJob &J, int kind, int *bpc)
 {
+    if (kind == kBasisResident) {
+        int nt = 0;
+        size_t lds = 0;
+        basis_fn k = (basis_fn)basis_r_kernel(S.o, S.nmax, J.nu, J.q, lidx_bytes(S.max_nat, S.max_lnnz),
+                                              &nt, &lds);
+        if (!k) return hipErrorInvalidConfiguration;
+        return occupancy_of(k, nt, lds, bpc);
+    }
     const size_t smem = basis_smem_bytes(S.nmax, J.nu, kind, S.o) +
                         (J.lidx ? lidx_bytes(S.max_nat, S.max_lnnz) : 0);
     if (kind == kBasisOnchip) {

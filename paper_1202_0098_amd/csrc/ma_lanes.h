@@ -3,7 +3,9 @@
 // them.  None touches LDS.
 #pragma once
 
-#include "ma_device.h"
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 namespace ma {
 
@@ -27,6 +29,7 @@ __device__ __forceinline__ double dpp(double v)
 
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // lane 7 - l of 8, 15 - l of 16
+constexpr int kDppRor8 = 0x128;                            // lane l ^ 8 of 16
 
 // a: lanes of the even rows (lower half) of a, then those of b; b: the odd
 // rows (upper half) of both.  The sum of the two is the exchange step of a
@@ -88,11 +91,30 @@ __device__ __forceinline__ double sum_across(double v)
     return v;
 }
 
-// lane l's value (l uniform), in every lane
-__device__ __forceinline__ double lane_value(double v, int l)
+// a value that every lane holds, as a scalar
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Transposed reduction of eight values per lane over the wavefront:
+// afterwards v[0] of lane l holds the total of value tr_index<8>(l).  The two
+// widest exchanges, most of the work, are lane swaps without selects.
+__device__ __forceinline__ void lane_reduce8(double (&v)[8])
 {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                            __builtin_amdgcn_readlane(__double2loint(v), l));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        swap32(v[k], v[k + 4]);
+        v[k] += v[k + 4];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        swap16(v[k], v[k + 2]);
+        v[k] += v[k + 2];
+    }
+    const bool hi = (threadIdx.x & 8) != 0;
+    const double send = hi ? v[0] : v[1], keep = hi ? v[1] : v[0];
+    v[0] = keep + dpp<kDppRor8>(send);
+    v[0] += dpp<kDppHalfMirror>(v[0]);
+    v[0] += dpp<kDppXor2>(v[0]);
+    v[0] += dpp<kDppXor1>(v[0]);
 }
 
 // 1 / sqrt(x) for normal x > 0: v_rsq_f64 (about 1e-8) and one third-order
