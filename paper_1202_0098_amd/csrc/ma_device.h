@@ -172,11 +172,12 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 1 / (1 + e^x) without overflow, one exponential and one division for either
+// sign of x
 __device__ __forceinline__ double fermi(double x)
 {
-    if (x <= 0.0) return 1.0 / (1.0 + exp(x));
-    double e = exp(-x);
-    return e / (1.0 + e);
+    const double e = exp(-fabs(x));
+    return (x <= 0.0 ? 1.0 : e) / (1.0 + e);
 }
 
 // ------------------------------------------------------------------------
@@ -2307,18 +2308,61 @@ __global__ void __launch_bounds__(NT) k_basis_s(DevSystem S, DevJob J)
 __global__ void k_reset(int *queue, int *fail, int reset_fail)
 {
     for (int k = 0; k < kMaxQueues; ++k) queue[k] = 0;
-    if (reset_fail) fail[0] = INT_MAX;
+    if (reset_fail) {
+        fail[0] = INT_MAX;
+        fail[1] = 0;   // the bracket kernel's completion counter
+    }
 }
 
 // ------------------------------------------------------------------------
 // Fermi weighting and the chemical potential
 // ------------------------------------------------------------------------
+// Whether this workgroup is the last of the grid to get here (a device-scope
+// counter, cleared by the last one); what the first wavefronts of the others
+// wrote before is visible.  One fence per workgroup: it writes back the L2 of its
+// XCD, and as one per wavefront it was most of a small kernel's time.
+__device__ __forceinline__ bool last_block(int *counter, int *s_last)
+{
+    if (threadIdx.x == 0) {
+        __threadfence();
+        *s_last = atomicAdd(counter, 1) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!*s_last) return false;
+    __threadfence();
+    if (threadIdx.x == 0) *counter = 0;
+    return true;
+}
+
+// state of the K-section, after the partial sums: completion counter, passes done
+__host__ __device__ inline int *count_state(double *partial)
+{
+    return reinterpret_cast<int *>(partial + kCountBlocks * kBisectTrials);
+}
+
 // Bracket of the chemical potential: [min eps - 50 kT, max eps + 50 kT] over
-// the accepted Ritz values.  Per-block extremes, then one block combines them.
+// the accepted Ritz values.  Per-block extremes; the last block combines them
+// and starts the K-section.
 __global__ void __launch_bounds__(256) k_minmax(const double *eps, const int32_t *stats, int ncols,
-                                                int nu, double *part)
+                                                int nu, double kT, double *lohi, double *part,
+                                                int *counter)
 {
     __shared__ double smin[4], smax[4];
+    __shared__ int s_last;
+    auto extremes = [&](double &lo, double &hi) __attribute__((always_inline)) {
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, off, 64));
+            hi = fmax(hi, __shfl_xor(hi, off, 64));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            smin[threadIdx.x >> 6] = lo;
+            smax[threadIdx.x >> 6] = hi;
+        }
+        __syncthreads();
+        lo = fmin(fmin(smin[0], smin[1]), fmin(smin[2], smin[3]));
+        hi = fmax(fmax(smax[0], smax[1]), fmax(smax[2], smax[3]));
+        __syncthreads();
+    };
     double lo = INFINITY, hi = -INFINITY;
     const int64_t total = (int64_t)ncols * nu;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
@@ -2329,72 +2373,64 @@ __global__ void __launch_bounds__(256) k_minmax(const double *eps, const int32_t
             hi = fmax(hi, eps[e]);
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, off, 64));
-        hi = fmax(hi, __shfl_xor(hi, off, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        smin[threadIdx.x >> 6] = lo;
-        smax[threadIdx.x >> 6] = hi;
-    }
-    __syncthreads();
+    extremes(lo, hi);
     if (threadIdx.x == 0) {
-        for (int k = 1; k < 4; ++k) {
-            lo = fmin(lo, smin[k]);
-            hi = fmax(hi, smax[k]);
-        }
-        lo = fmin(lo, smin[0]);
-        hi = fmax(hi, smax[0]);
         part[2 * blockIdx.x] = lo;
         part[2 * blockIdx.x + 1] = hi;
     }
-}
-
-__global__ void __launch_bounds__(64) k_minmax_final(const double *part, int nblocks, double kT,
-                                                     double *lohi, unsigned *done)
-{
-    double lo = INFINITY, hi = -INFINITY;
-    for (int b = threadIdx.x; b < nblocks; b += 64) {
-        lo = fmin(lo, part[2 * b]);
-        hi = fmax(hi, part[2 * b + 1]);
+    if (!last_block(counter, &s_last)) return;
+    lo = INFINITY;
+    hi = -INFINITY;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
+        lo = fmin(lo, __builtin_nontemporal_load(part + 2 * b));
+        hi = fmax(hi, __builtin_nontemporal_load(part + 2 * b + 1));
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, off, 64));
-        hi = fmax(hi, __shfl_xor(hi, off, 64));
-    }
+    extremes(lo, hi);
     if (threadIdx.x == 0) {
         lohi[0] = lo - 50.0 * kT;
         lohi[1] = hi + 50.0 * kT;
-        *done = 0u;   // the K-section passes' completion counter
+        count_state(part)[0] = count_state(part)[1] = 0;
     }
 }
 
-// completion counter of the K-section passes: the word after the partial sums
-__host__ __device__ inline unsigned *count_done(double *partial)
-{
-    return reinterpret_cast<unsigned *>(partial + kCountBlocks * kBisectTrials);
-}
+// One pass of the search for sum_j sum_a f((eps_a - mu)/kT) w_a = n_target on
+// the bracket lohi.  While the bracket is wider than kT / 8, a K-section step:
+// the electron count at kBisectTrials equally spaced trial potentials, and the
+// bracket narrows to the first whose count reaches the target (the count need
+// not be monotone: a weight can be negative).  Below that width the count is a
+// power series to rounding: with t = (mu - c)/kT about the bracket's centre c,
+// |t| <= 1/16, g(t) = f(x - t) solves g' = g (1 - g), so that its coefficients
+// follow from (k + 1) c_{k+1} = c_k - sum_i c_i c_{k-i}, and the terms past
+// order kSeries are below (1 / 16 pi)^{kSeries+1} = 2e-17 of the weight (the
+// poles of f lie at distance pi).  One pass sums the coefficients over the Ritz
+// pairs, the rest of the kBisectPasses K-section steps run on the polynomial,
+// and the passes that are left return at once.
+// Every block writes its partial sums; the last to finish adds them in a fixed
+// order.  A pass is a chain of latencies (two reductions, a counter).  The whole
+// search on 4,096, 491,520 and 1,866,240 Ritz pairs with kT = 0.1 to 0.2 eV (three
+// K-section steps, the series, ten empty passes): 79, 149 and 329 us; as
+// kBisectPasses K-section steps 262, 800 and 2,120 us.
+constexpr int kSeries = 9;
 
-// Electron count sum_j sum_a f((eps_a - mu_t)/kT) w_a for the kBisectTrials
-// trial potentials mu_t equally spaced inside (lo, hi); one partial per block.
-// One K-section pass: every block evaluates the electron count at KT_
-// equally spaced trial potentials over its share of the Ritz pairs and
-// writes its partial sums; the last block to finish (a device-scope counter)
-// sums the partials of all blocks in a fixed order and narrows the bracket
-// to the first trial whose count reaches the target, then clears the
-// counter for the next pass.
 __global__ void __launch_bounds__(256) k_count(const double *eps, const double *wts,
                                                const int32_t *stats, int ncols, int nu,
                                                double kT, double n_target, double *lohi,
-                                               double *partial, unsigned *done)
+                                               double *partial)
 {
     constexpr int KT_ = kBisectTrials;
-    __shared__ double sred[4][KT_];
-    __shared__ int last;
+    static_assert(KT_ == 15 && kSeries + 1 <= KT_, "sixteen values per reduction");
+    __shared__ double sred[4][16], poly[16];
+    __shared__ int s_last;
+    int *state = count_state(partial);
+    const int passes = state[1];
+    if (passes >= kBisectPasses) return;
     const double lo = lohi[0], hi = lohi[1];
-    double acc[KT_];
+    const bool series = hi - lo <= 0.125 * kT;
+    const double centre = 0.5 * (lo + hi), rkT = 1.0 / kT;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double acc[16];
 #pragma unroll
-    for (int t = 0; t < KT_; ++t) acc[t] = 0.0;
+    for (int t = 0; t < 16; ++t) acc[t] = 0.0;
     const int64_t total = (int64_t)ncols * nu;
     const int64_t chunk = (total + gridDim.x - 1) / gridDim.x;
     const int64_t e0 = blockIdx.x * chunk, e1 = min(total, e0 + chunk);
@@ -2402,51 +2438,74 @@ __global__ void __launch_bounds__(256) k_count(const double *eps, const double *
         const int64_t c = e / nu;
         if (e - c * nu >= stats[c * kStats]) continue;
         const double ev = eps[e], w = wts[e];
+        if (series) {
+            double g[kSeries + 1];
+            g[0] = fermi((ev - centre) * rkT);
 #pragma unroll
-        for (int t = 0; t < KT_; ++t) {
-            const double mu = lo + (hi - lo) * (double)(t + 1) / (double)(KT_ + 1);
-            acc[t] += fermi((ev - mu) / kT) * w;
+            for (int k = 0; k < kSeries; ++k) {
+                double s = g[k];
+#pragma unroll
+                for (int i = 0; i <= k; ++i) s -= g[i] * g[k - i];
+                g[k + 1] = s * (1.0 / (k + 1));
+            }
+#pragma unroll
+            for (int k = 0; k <= kSeries; ++k) acc[k] += g[k] * w;
+        } else {
+#pragma unroll
+            for (int t = 0; t < KT_; ++t) {
+                const double mu = lo + (hi - lo) * (double)(t + 1) / (double)(KT_ + 1);
+                acc[t] += fermi((ev - mu) / kT) * w;
+            }
         }
     }
+    // sixteen totals of the workgroup, in sred[0]
+    auto block_totals = [&]() __attribute__((always_inline)) {
+        wave_transpose_reduce<16>(acc);
+        if (tr_writer<16>(lane)) sred[wv][tr_index<16>(lane)] = acc[0];
+        __syncthreads();
+        if (threadIdx.x < 16)
+            sred[0][lane] = ((sred[0][lane] + sred[1][lane]) + sred[2][lane]) + sred[3][lane];
+        __syncthreads();
+    };
+    block_totals();
+    if (threadIdx.x < KT_) partial[blockIdx.x * KT_ + threadIdx.x] = sred[0][threadIdx.x];
+    if (!last_block(state, &s_last)) return;
+    // fixed order: thread b adds blocks b, b + 256, ...; then lanes, then waves 0..3
 #pragma unroll
-    for (int t = 0; t < KT_; ++t) {
-        const double v = wave_sum(acc[t]);
-        if ((threadIdx.x & 63) == 0) sred[threadIdx.x >> 6][t] = v;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < KT_; t += blockDim.x)
-        partial[blockIdx.x * KT_ + t] = ((sred[0][t] + sred[1][t]) + sred[2][t]) + sred[3][t];
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    // fixed order: thread b adds blocks b, b + 256, ...; then wavefronts, then waves 0..3
-#pragma unroll
-    for (int t = 0; t < KT_; ++t) acc[t] = 0.0;
+    for (int t = 0; t < 16; ++t) acc[t] = 0.0;
     for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x)
 #pragma unroll
         for (int t = 0; t < KT_; ++t) acc[t] += __builtin_nontemporal_load(partial + b * KT_ + t);
     __syncthreads();
-#pragma unroll
-    for (int t = 0; t < KT_; ++t) {
-        const double v = wave_sum(acc[t]);
-        if ((threadIdx.x & 63) == 0) sred[threadIdx.x >> 6][t] = v;
-    }
+    block_totals();
+    if (threadIdx.x < 16) poly[lane] = sred[0][lane];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int first = KT_;
-        for (int t = 0; t < KT_; ++t)
-            if (((sred[0][t] + sred[1][t]) + sred[2][t]) + sred[3][t] >= n_target) {
-                first = t;
-                break;
-            }
-        const double nlo = first == 0 ? lo : lo + (hi - lo) * (double)first / (double)(KT_ + 1);
-        const double nhi = first == KT_ ? hi : lo + (hi - lo) * (double)(first + 1) / (double)(KT_ + 1);
-        lohi[0] = nlo;
-        lohi[1] = nhi;
-        *done = 0u;
+    if (wv != 0) return;
+    // lane t holds trial t's count
+    const int trial = lane < KT_ ? lane : KT_ - 1;
+    double l = lo, h = hi;
+    int done = passes;
+    do {
+        double count = poly[trial];
+        if (series) {
+            const double mu = l + (h - l) * (double)(trial + 1) / (double)(KT_ + 1);
+            const double t = (mu - centre) * rkT;
+            count = poly[kSeries];
+#pragma unroll
+            for (int k = kSeries - 1; k >= 0; --k) count = fma(count, t, poly[k]);
+        }
+        const unsigned long long reach = __ballot(lane < KT_ && count >= n_target);
+        const int first = reach ? __ffsll((long long)reach) - 1 : KT_;
+        const double nl = first == 0 ? l : l + (h - l) * (double)first / (double)(KT_ + 1);
+        const double nh = first == KT_ ? h : l + (h - l) * (double)(first + 1) / (double)(KT_ + 1);
+        l = nl;
+        h = nh;
+        ++done;
+    } while (series && done < kBisectPasses);
+    if (lane == 0) {
+        lohi[0] = l;
+        lohi[1] = h;
+        state[1] = done;
     }
 }
 
@@ -2518,9 +2577,8 @@ __global__ void __launch_bounds__(1024) k_sum2(const double *a, const double *b,
 {
     __shared__ double sa[16], sb[16];
     double x = 0.0, y = 0.0;
-    const int64_t chunk = (n + blockDim.x - 1) / blockDim.x;
-    const int64_t e0 = threadIdx.x * chunk, e1 = min((int64_t)n, e0 + chunk);
-    for (int64_t e = e0; e < e1; ++e) {
+#pragma unroll 8
+    for (int e = threadIdx.x; e < n; e += 1024) {
         x += a[e];
         y += b[e];
     }

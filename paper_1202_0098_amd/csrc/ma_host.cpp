@@ -1477,8 +1477,8 @@ hipError_t enqueue_post(ma_ctx *ctx, const Plan &P)
     const ma::DevJob &J = P.J;
     hipError_t e;
     if (P.bisect) {
-        if ((e = ma::launch_minmax(J.eps, J.stats, J.ncols, J.nu, P.kT, P.lohi, P.partial, st)) !=
-            hipSuccess) return e;
+        if ((e = ma::launch_minmax(J.eps, J.stats, J.ncols, J.nu, P.kT, P.lohi, P.partial,
+                                   J.fail + 1, st)) != hipSuccess) return e;
         if ((e = ma::launch_bisect(J.eps, J.wts, J.stats, J.ncols, J.nu, P.kT, P.n_target,
                                    P.lohi, P.partial, st)) != hipSuccess) return e;
         if ((e = ma::launch_rho(S, J, P.lohi, P.kT, P.rho, P.pi, J.Ecol, J.Ncol, st)) != hipSuccess)
@@ -1700,7 +1700,7 @@ MA_API ma_status ma_find_mu(ma_ctx *ctx, double n_target, double kT, double spin
     HIPCHK(ctx, ctx->after_caller(), "stream order");
     HIPCHK(ctx, hipEventRecord(ctx->ev0, st), "event");
     HIPCHK(ctx, ma::launch_minmax(J.eps, J.stats, J.ncols, J.nu, kT, ctx->last_lohi,
-                                  ctx->last_partial, st), "bracket");
+                                  ctx->last_partial, J.fail + 1, st), "bracket");
     HIPCHK(ctx, ma::launch_bisect(J.eps, J.wts, J.stats, J.ncols, J.nu, kT, n_target,
                                   ctx->last_lohi, ctx->last_partial, st), "bisection");
     HIPCHK(ctx, ma::launch_rho(S, J, ctx->last_lohi, kT, out->rho, out->pi, J.Ecol, J.Ncol, st),

@@ -65,7 +65,8 @@ struct DevJob {
     int *queue;                // work counters, one per queue (reset before each chunk)
     int nqueues;               // 1, or 8 (one per XCD)
     const int32_t *qbounds;    // nqueues + 1 absolute offsets into order, this chunk
-    int *fail;                 // [0] = first failing c (INT_MAX none)
+    int *fail;                 // [0] = first failing c (INT_MAX none), [1] = completion
+                               // counter of the bracket kernel
     const int32_t *gstart;     // atom-group kernel: columns of group g are order positions
                                // gstart[g] .. gstart[g+1]
     int lidx;                  // 1: the basis kernel stages each region's local block
@@ -146,8 +147,9 @@ hipError_t basis_occupancy(const DevSystem &S, const DevJob &J, int kind, int *b
 hipError_t launch_eig(const DevSystem &S, const DevJob &J, hipStream_t st);
 
 // Fermi weighting, chemical potential, reductions.
+// (counter: a zeroed device word, left zero)
 hipError_t launch_minmax(const double *eps, const int32_t *stats, int ncols, int nu,
-                         double kT, double *lohi, double *partial, hipStream_t st);
+                         double kT, double *lohi, double *partial, int *counter, hipStream_t st);
 hipError_t launch_bisect(const double *eps, const double *wts, const int32_t *stats,
                          int ncols, int nu, double kT, double n_target, double *lohi,
                          double *partial, hipStream_t st);

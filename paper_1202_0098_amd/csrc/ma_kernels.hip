@@ -204,12 +204,10 @@ int count_grid(int ncols, int nu)
 }
 
 hipError_t launch_minmax(const double *eps, const int32_t *stats, int ncols, int nu, double kT,
-                         double *lohi, double *partial, hipStream_t st)
+                         double *lohi, double *partial, int *counter, hipStream_t st)
 {
-    const int grid = count_grid(ncols, nu);
-    hipLaunchKernelGGL(k_minmax, dim3(grid), dim3(256), 0, st, eps, stats, ncols, nu, partial);
-    hipLaunchKernelGGL(k_minmax_final, dim3(1), dim3(64), 0, st, partial, grid, kT, lohi,
-                       count_done(partial));
+    hipLaunchKernelGGL(k_minmax, dim3(count_grid(ncols, nu)), dim3(256), 0, st, eps, stats, ncols, nu,
+                       kT, lohi, partial, counter);
     return hipGetLastError();
 }
 
@@ -220,7 +218,7 @@ hipError_t launch_bisect(const double *eps, const double *wts, const int32_t *st
     const int grid = count_grid(ncols, nu);
     for (int pass = 0; pass < kBisectPasses; ++pass)
         hipLaunchKernelGGL(k_count, dim3(grid), dim3(256), 0, st, eps, wts, stats, ncols, nu, kT,
-                           n_target, lohi, partial, count_done(partial));
+                           n_target, lohi, partial);
     return hipGetLastError();
 }
 

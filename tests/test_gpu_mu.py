@@ -1,0 +1,56 @@
+"""The chemical-potential search against the same K-section (14 passes of 15 trial
+potentials, the first that reaches the target) done directly in numpy on the
+returned Ritz values and weights: from kT so small that the bracket never falls
+below kT / 8 (no series) to kT above the spectrum's width, and from an almost
+empty to an almost full count.
+
+N(mu) is summed to about 1e-15 of the total weight on both sides, so that mu
+agrees to that over dN/dmu; asserted to 1e-12 of the weight over the local slope,
+and never looser than 1e-6 kT."""
+
+import math
+
+import numpy as np
+import pytest
+
+from paper_1202_0098_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _count(mu, e, w, kT):
+    x = (e[None, :] - np.atleast_1d(mu)[:, None]) / kT
+    t = np.exp(-np.abs(x))
+    return (np.where(x <= 0, 1.0, t) / (1.0 + t)) @ w
+
+
+@pytest.mark.parametrize("kT", [1e-9, 1e-4, 0.1, 0.7, 40.0])
+@pytest.mark.parametrize("fill", [0.02, 0.5, 0.97])
+def test_mu(kT, fill):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    s = synth.config_diamond64()
+    nu, target = s.p + s.q, fill * s.M
+    print(f"[gpu-case] diamond64 kT={kT} fill={fill}", flush=True)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    eps = torch.zeros(s.M * nu, dtype=torch.float64, device="cuda")
+    wts = torch.zeros_like(eps)
+    r = ctx.solve_columns(None, s.p, s.q, kT=kT, eps=eps, wts=wts, opts=ma.default_opts(n_target=target))
+    e, w = eps.cpu().numpy(), wts.cpu().numpy()
+    lo, hi = e.min() - 50 * kT, e.max() + 50 * kT
+    for _ in range(14):
+        mus = lo + (hi - lo) * np.arange(1, 16) / 16
+        reach = np.nonzero(_count(mus, e, w, kT) >= target)[0]
+        first = reach[0] if len(reach) else 15
+        lo, hi = (mus[first - 1] if first > 0 else lo), (mus[first] if first < 15 else hi)
+    mu = 0.5 * (lo + hi)
+    d = 1e-3 * kT
+    slope = float(np.diff(_count([mu - d, mu + d], e, w, kT))[0] / (2 * d))
+    assert abs(r.mu - mu) <= max(4e-16 * abs(mu), min(1e-12 * s.M / max(slope, 1e-300), 1e-6 * kT))
+    # the same search again on the kept data, at another temperature and back
+    ctx.find_mu(target, 2 * kT)
+    assert ctx.find_mu(target, kT).mu == r.mu
+    ctx.close()
