@@ -357,7 +357,7 @@ def device_source_digest():
     csrc = os.path.join(ROOT, "paper_1202_0098_amd", "csrc")
     h = hashlib.sha256()
     for fn in sorted(os.listdir(csrc)):
-        if fn.endswith(".hip") or fn in ("ma_device.h", "ma_internal.h"):
+        if fn.endswith(".hip") or fn in ("ma_device.h", "ma_internal.h", "ma_lanes.h"):
             with open(os.path.join(csrc, fn), "rb") as f:
                 h.update(fn.encode() + b"\0" + f.read())
     return h.hexdigest()

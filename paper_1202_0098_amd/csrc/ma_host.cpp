@@ -2045,13 +2045,13 @@ hipError_t net_forward_f32(ma_ctx *ctx, const float *x, int64_t n, float *y, hip
     auto &N = ctx->net;
     const float *p = N.params.as<float>();
     hipError_t e = ma::launch_gemm((int)n, N.nh, N.nf, x, N.nf, 1, nullptr, p + N.oW1, N.nh, 1,
-                                   p + N.ob1, 0.f, N.A1.as<float>(), N.nh, N.Z1.as<float>(), st);
+                                   p + N.ob1, 0.f, N.A1.as<float>(), N.nh, N.Z1.as<float>(), nullptr, st);
     if (e == hipSuccess)
         e = ma::launch_gemm((int)n, N.nh, N.nh, N.A1.as<float>(), N.nh, 1, nullptr, p + N.oW2, N.nh, 1,
-                            p + N.ob2, 0.f, N.A2.as<float>(), N.nh, N.Z2.as<float>(), st);
+                            p + N.ob2, 0.f, N.A2.as<float>(), N.nh, N.Z2.as<float>(), nullptr, st);
     if (e == hipSuccess)
         e = ma::launch_gemm((int)n, N.no, N.nh, N.A2.as<float>(), N.nh, 1, nullptr, p + N.oW3, N.no, 1,
-                            p + N.ob3, 0.f, y, N.no, nullptr, st);
+                            p + N.ob3, 0.f, y, N.no, nullptr, nullptr, st);
     return e;
 }
 
@@ -2072,18 +2072,13 @@ ma_status net_train_core(ma_ctx *ctx, const float *x, const float *t, const int3
     const float *X = x, *T = t;
     if (idx) {
         // the device indices are checked by the gather: one outside the
-        // table fails the call before any update
+        // table fails the call, and the update is not made
         HIPCHK(ctx, N.bad.reserve(sizeof(int)), "index flag");
         HIPCHK(ctx, hipMemsetAsync(N.bad.p, 0, sizeof(int), st), "index flag");
         HIPCHK(ctx, ma::launch_gather_rows(x, idx, n, N.nf, n_rows, N.Xb.as<float>(),
                                            N.bad.as<int>(), st), "gather");
         HIPCHK(ctx, ma::launch_gather_rows(t, idx, n, N.no, n_rows, N.Tb.as<float>(),
                                            N.bad.as<int>(), st), "gather");
-        int bad = 0;
-        HIPCHK(ctx, hipMemcpyAsync(&bad, N.bad.p, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
-        HIPCHK(ctx, hipStreamSynchronize(st), "gather");
-        if (bad) return ctx->fail(MA_EINVAL, "a row index is outside the table of %lld rows",
-                                  (long long)n_rows);
         X = N.Xb.as<float>();
         T = N.Tb.as<float>();
     }
@@ -2094,34 +2089,37 @@ ma_status net_train_core(ma_ctx *ctx, const float *x, const float *t, const int3
                                N.partial.as<double>(), 256, st), "loss");
     // layer 3
     HIPCHK(ctx, ma::launch_gemm(N.nh, N.no, nn, N.A2.as<float>(), 1, N.nh, nullptr, N.dY.as<float>(),
-                                N.no, 1, nullptr, 0.f, g + N.oW3, N.no, nullptr, st), "backward");
+                                N.no, 1, nullptr, 0.f, g + N.oW3, N.no, nullptr, nullptr, st), "backward");
     HIPCHK(ctx, ma::launch_colsum(N.dY.as<float>(), n, N.no, g + N.ob3, st), "backward");
     HIPCHK(ctx, ma::launch_gemm(nn, N.nh, N.no, N.dY.as<float>(), N.no, 1, nullptr, p + N.oW3, 1, N.no,
-                                nullptr, 0.f, N.dA.as<float>(), N.nh, nullptr, st), "backward");
+                                nullptr, 0.f, N.dA.as<float>(), N.nh, nullptr, N.Z2.as<float>(), st), "backward");
     // layer 2
-    HIPCHK(ctx, ma::launch_silu_bwd(N.dA.as<float>(), N.Z2.as<float>(), n * N.nh, st), "backward");
     HIPCHK(ctx, ma::launch_gemm(N.nh, N.nh, nn, N.A1.as<float>(), 1, N.nh, nullptr, N.dA.as<float>(),
-                                N.nh, 1, nullptr, 0.f, g + N.oW2, N.nh, nullptr, st), "backward");
+                                N.nh, 1, nullptr, 0.f, g + N.oW2, N.nh, nullptr, nullptr, st), "backward");
     HIPCHK(ctx, ma::launch_colsum(N.dA.as<float>(), n, N.nh, g + N.ob2, st), "backward");
     float *dA1 = N.Z2.as<float>();   // Z2 is no longer needed
     HIPCHK(ctx, ma::launch_gemm(nn, N.nh, N.nh, N.dA.as<float>(), N.nh, 1, nullptr, p + N.oW2, 1, N.nh,
-                                nullptr, 0.f, dA1, N.nh, nullptr, st), "backward");
+                                nullptr, 0.f, dA1, N.nh, nullptr, N.Z1.as<float>(), st), "backward");
     // layer 1
-    HIPCHK(ctx, ma::launch_silu_bwd(dA1, N.Z1.as<float>(), n * N.nh, st), "backward");
     HIPCHK(ctx, ma::launch_gemm(N.nf, N.nh, nn, X, 1, N.nf, nullptr, dA1, N.nh, 1, nullptr, 0.f,
-                                g + N.oW1, N.nh, nullptr, st), "backward");
+                                g + N.oW1, N.nh, nullptr, nullptr, st), "backward");
     HIPCHK(ctx, ma::launch_colsum(dA1, n, N.nh, g + N.ob1, st), "backward");
-    if (update) {
-        N.step += 1;
+    if (update)
         HIPCHK(ctx, ma::launch_adam(p, g, N.m.as<float>(), N.v.as<float>(), N.P, lr, 0.9f, 0.999f,
-                                    1e-8f, N.step, st), "adam");
-        N.bf16_dirty = true;
-    }
+                                    1e-8f, N.step + 1, idx ? N.bad.as<int>() : nullptr, st), "adam");
+    int bad = 0;
+    if (idx) HIPCHK(ctx, hipMemcpyAsync(&bad, N.bad.p, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
     double part[256];
     HIPCHK(ctx, hipMemcpyAsync(part, N.partial.p, sizeof part, hipMemcpyDeviceToHost, st), "copy");
     if (grad_host)
         HIPCHK(ctx, hipMemcpyAsync(grad_host, g, sizeof(float) * N.P, hipMemcpyDeviceToHost, st), "copy");
     HIPCHK(ctx, hipStreamSynchronize(st), "training step");
+    if (bad) return ctx->fail(MA_EINVAL, "a row index is outside the table of %lld rows",
+                              (long long)n_rows);
+    if (update) {
+        N.step += 1;
+        N.bf16_dirty = true;
+    }
     if (loss) {
         double sum = 0.0;
         for (int b = 0; b < 256; ++b) sum += part[b];

@@ -198,12 +198,12 @@ hipError_t launch_mlp_infer(const float *X, int64_t n, int nf, int nf_pad, int n
                             hipStream_t st);
 hipError_t launch_gemm(int M, int N, int K, const float *A, int64_t sa0, int64_t sa1,
                        const int32_t *gather, const float *B, int64_t sb0, int64_t sb1,
-                       const float *bias, float beta, float *C, int64_t ldc, float *Z, hipStream_t st);
+                       const float *bias, float beta, float *C, int64_t ldc, float *Z,
+                       const float *Zg, hipStream_t st);
 hipError_t launch_mse(const float *Y, const float *T, const int32_t *gather, int64_t n, int no,
                       float *dY, double *partial, int nblocks, hipStream_t st);
-hipError_t launch_silu_bwd(float *G, const float *Z, int64_t total, hipStream_t st);
 hipError_t launch_colsum(const float *G, int64_t n, int m, float *db, hipStream_t st);
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, int64_t count, float lr,
-                       float b1, float b2, float eps, int step, hipStream_t st);
+                       float b1, float b2, float eps, int step, const int *bad, hipStream_t st);
 
 }  // namespace ma

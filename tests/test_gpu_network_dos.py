@@ -1,0 +1,78 @@
+"""The network products at the edges of their tiles: batches around the 16-row
+tiles and the splits of K, and what a row index outside the table does."""
+
+import numpy as np
+import pytest
+
+from paper_1202_0098_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    ctx = ma.Context(0)
+    s = synth.config_diamond64()
+    ctx.build_tb(s)
+    ctx.mlp_init(seed=3)
+    yield torch, ma, ctx, s
+    ctx.close()
+
+
+# the sums are FP32 over at most 1,000 rows or 256 inputs in three layers:
+# 3 sqrt(1000) 2^-24 = 6e-6
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 1000])
+def test_gradient_at_tile_edges(env, n):
+    torch, ma, ctx, s = env
+    from oracle import mlp
+    sh = ctx.mlp_shape()
+    rng = np.random.default_rng(n)
+    X = rng.normal(size=(n, sh["n_in"])).astype(np.float32)
+    T = (rng.normal(size=(n, sh["n_out"])) * 0.1).astype(np.float32)
+    loss, g = ctx.mlp_loss_grad(torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda(), n)
+    loss_o, g_o = mlp.loss_grad(ctx.mlp_get_params().astype(np.float64), X.astype(np.float64),
+                                T.astype(np.float64), (sh["n_in"], sh["n_hidden"], sh["n_out"]))
+    print(f"[gpu-case] n {n}: loss {abs(loss - loss_o) / loss_o:.1e} "
+          f"gradient {np.linalg.norm(g - g_o) / np.linalg.norm(g_o):.1e}", flush=True)
+    assert abs(loss - loss_o) <= 1e-5 * loss_o
+    assert np.linalg.norm(g - g_o) <= 1e-5 * np.linalg.norm(g_o)
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 64, 100])
+def test_inference_rows_are_independent(env, n):
+    torch, ma, ctx, s = env
+    sh = ctx.mlp_shape()
+    rng = np.random.default_rng(7)
+    X = torch.from_numpy(rng.normal(size=(100, sh["n_in"])).astype(np.float32)).cuda()
+    full = torch.zeros(100, sh["n_out"], dtype=torch.float32, device="cuda")
+    ctx.mlp_forward(X, 100, full, bf16=True)
+    part = torch.full((101, sh["n_out"]), 7.0, dtype=torch.float32, device="cuda")
+    ctx.mlp_forward(X[100 - n:].contiguous(), n, part, bf16=True)
+    assert torch.equal(part[:n], full[100 - n:])
+    assert bool((part[n:] == 7.0).all())
+
+
+def test_an_index_outside_the_table_makes_no_update(env):
+    torch, ma, ctx, s = env
+    sh = ctx.mlp_shape()
+    X = torch.randn(20, sh["n_in"], device="cuda")
+    T = torch.randn(20, sh["n_out"], device="cuda")
+    before = ctx.mlp_get_params()
+    good = torch.arange(16, dtype=torch.int32, device="cuda")
+    for bad in (-1, 20):
+        idx = good.clone()
+        idx[5] = bad
+        with pytest.raises(Exception, match="outside the table"):
+            ctx.mlp_train_step(X, T, 16, 1e-3, idx=idx)
+        assert np.array_equal(ctx.mlp_get_params(), before)
+    # the step counter has not moved either: as from a fresh optimizer
+    ctx.mlp_train_step(X, T, 16, 1e-3, idx=good)
+    got = ctx.mlp_get_params()
+    ctx.mlp_init(seed=3)
+    ctx.mlp_train_step(X, T, 16, 1e-3, idx=good)
+    assert np.array_equal(ctx.mlp_get_params(), got)
+    ctx.mlp_init(seed=3)
