@@ -123,6 +123,7 @@ struct ma_ctx {
     int64_t sj_nreg = 0, sj_natoms_total = 0;
     int64_t nreg = 0, reg_atoms_total = 0;
     DevBuf dos_E, dos_part, dos_out;  // density-of-states buffers
+    DevBuf force_g;                   // force terms of the pattern blocks
     DevBuf blk_ptr, blk_col, Hd, Sd, Hf, Sf, reg_id, reg_off, reg_len, lrp_off, lrp, lblk, jloc,
         blk_loc;
     bool have_geo = false;            // neighbour descriptors were built
@@ -1732,9 +1733,10 @@ MA_API ma_status ma_forces(ma_ctx *ctx, const double *dH, const double *dS, cons
     HIPCHK(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     hipStream_t st = ctx->work_stream();
     HIPCHK(ctx, ctx->after_caller(), "stream order");
+    HIPCHK(ctx, ctx->force_g.reserve(sizeof(double) * 3 * (size_t)ctx->nblk), "forces");
     HIPCHK(ctx, ma::launch_forces(ctx->n_atoms, ctx->o, ctx->blk_ptr.as<int64_t>(),
                                   ctx->blk_col.as<int32_t>(), ctx->blk_t.as<int32_t>(), dH, dS, rho,
-                                  pi, spin, forces, st), "forces");
+                                  pi, spin, ctx->nblk, ctx->force_g.as<double>(), forces, st), "forces");
     HIPCHK(ctx, hipStreamSynchronize(st), "forces");
     return MA_OK;
 }

@@ -161,8 +161,8 @@ hipError_t launch_sum2(const double *a, const double *b, int n, double *out, hip
 // (ma_post.hip).
 hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32_t *blk_col,
                          const int32_t *blk_t, const double *dH, const double *dS,
-                         const double *rho, const double *pi, double spin, double *F,
-                         hipStream_t st);
+                         const double *rho, const double *pi, double spin, int64_t nblk,
+                         double *g, double *F, hipStream_t st);
 size_t dos_partial_doubles(int ncols, int nu, int nE);
 hipError_t launch_dos(const double *eps, const double *wts, const int32_t *stats, int ncols,
                       int nu, const double *E, int nE, double eta, double spin, double *part,

@@ -18,90 +18,153 @@ namespace ma {
 
 namespace {
 
-// One wavefront per atom X (persistent over the atoms):
 // F_X = spin sum over blocks k = (X, B), B != X, of g_k - g_T(k), where
 // g_k = sum_{r,c} rho_k[r][c] dH_k[:][r][c] - pi_k[r][c] dS_k[:][r][c] and
 // T(k) is the block (B, X).  Block k = (A, B) holds columns j = (A, r) at
 // rows i = (B, c); dH_k is the derivative of H_AB with respect to R_B, so
 // g_k enters F_A with + and F_B with -.
-__global__ void __launch_bounds__(64) k_forces(int n_atoms, int o, const int64_t *blk_ptr,
-                                               const int32_t *blk_col, const int32_t *blk_t,
-                                               const double *dH, const double *dS,
-                                               const double *rho, const double *pi, double spin,
-                                               double *F)
+//
+// First g_k: LPB lanes per block, which reads every value once.  Bound by
+// those bytes (64 o^2 per block): 2,048 spd atoms 86 us and 4 us for the sum below;
+// one wavefront per atom over its blocks and their transposes, which read every
+// block twice, took 122 us.
+template <int LPB>
+__global__ void __launch_bounds__(256) k_block_forces(int64_t nblk, int oo, const double *dH,
+                                                      const double *dS, const double *rho,
+                                                      const double *pi, double *g)
 {
-    const int lane = threadIdx.x;
-    const int oo = o * o;
-    for (int X = blockIdx.x; X < n_atoms; X += gridDim.x) {
+    constexpr int BPW = 256 / LPB;   // blocks per workgroup
+    const int l = threadIdx.x % LPB;
+    for (int64_t k = (int64_t)blockIdx.x * BPW + threadIdx.x / LPB; k - threadIdx.x / LPB < nblk;
+         k += (int64_t)gridDim.x * BPW) {
         double f0 = 0.0, f1 = 0.0, f2 = 0.0;
-        for (int64_t k = blk_ptr[X]; k < blk_ptr[X + 1]; ++k) {
-            if (blk_col[k] == X) continue;
-            const int64_t kt = blk_t[k];
-            for (int e = lane; e < oo; e += 64) {
-                const double ra = rho[k * oo + e], pa = pi[k * oo + e];
-                const double rb = rho[kt * oo + e], pb = pi[kt * oo + e];
-                const double *ha = dH + k * 3 * oo + e, *sa = dS + k * 3 * oo + e;
-                const double *hb = dH + kt * 3 * oo + e, *sb = dS + kt * 3 * oo + e;
-                f0 += (ra * ha[0] - pa * sa[0]) - (rb * hb[0] - pb * sb[0]);
-                f1 += (ra * ha[oo] - pa * sa[oo]) - (rb * hb[oo] - pb * sb[oo]);
-                f2 += (ra * ha[2 * oo] - pa * sa[2 * oo]) - (rb * hb[2 * oo] - pb * sb[2 * oo]);
+        if (k < nblk)
+#pragma unroll 2
+            for (int e = l; e < oo; e += LPB) {
+                const double r = rho[k * oo + e], p = pi[k * oo + e];
+                const double *h = dH + k * 3 * oo + e, *s = dS + k * 3 * oo + e;
+                f0 += r * h[0] - p * s[0];
+                f1 += r * h[oo] - p * s[oo];
+                f2 += r * h[2 * oo] - p * s[2 * oo];
             }
-        }
-        f0 = wave_sum(f0);
-        f1 = wave_sum(f1);
-        f2 = wave_sum(f2);
-        if (lane == 0) {
-            F[3 * (int64_t)X] = spin * f0;
-            F[3 * (int64_t)X + 1] = spin * f1;
-            F[3 * (int64_t)X + 2] = spin * f2;
-        }
+        f0 = sum_within<LPB>(f0);
+        f1 = sum_within<LPB>(f1);
+        f2 = sum_within<LPB>(f2);
+        if (l < 3 && k < nblk) g[3 * k + l] = l == 0 ? f0 : l == 1 ? f1 : f2;
     }
 }
 
-constexpr int kDosChunk = 8192;   // Ritz pairs per workgroup of the DOS kernel
-constexpr int kDosTile = 256;     // energies per workgroup
+// Then the sum over an atom's blocks, one wavefront per atom.
+__global__ void __launch_bounds__(256) k_forces(int n_atoms, const int64_t *blk_ptr,
+                                                const int32_t *blk_col, const int32_t *blk_t,
+                                                const double *g, double spin, double *F)
+{
+    const int lane = threadIdx.x & 63;
+    for (int X = blockIdx.x * 4 + (threadIdx.x >> 6); X < n_atoms; X += gridDim.x * 4) {
+        double f0 = 0.0, f1 = 0.0, f2 = 0.0;
+        for (int64_t k = blk_ptr[X] + lane; k < blk_ptr[X + 1]; k += 64) {
+            if (blk_col[k] == X) continue;
+            const double *a = g + 3 * k, *b = g + 3 * (int64_t)blk_t[k];
+            f0 += a[0] - b[0];
+            f1 += a[1] - b[1];
+            f2 += a[2] - b[2];
+        }
+        f0 = sum_within<64>(f0);
+        f1 = sum_within<64>(f1);
+        f2 = sum_within<64>(f2);
+        if (lane < 3) F[3 * (int64_t)X + lane] = spin * (lane == 0 ? f0 : lane == 1 ? f1 : f2);
+    }
+}
+
+constexpr int kDosStage = 1024;   // Ritz pairs staged at a time by the DOS kernel
+constexpr int kDosTile = 512;     // energies per workgroup, two per thread
+
+// Ritz pairs per workgroup: stages of 1,024 until the launch has 2,048
+// workgroups, at most eight (which bounds the partial sums)
+int64_t dos_chunk(int64_t npairs, int nE)
+{
+    const int64_t wgs = (npairs + kDosStage - 1) / kDosStage * ((nE + kDosTile - 1) / kDosTile);
+    return kDosStage * std::max<int64_t>(1, std::min<int64_t>(8, wgs / 2048));
+}
 
 // Partial DOS of one chunk of Ritz pairs (staged in LDS) at a tile of
-// energies: part[chunk][E] (thread t takes energy tile * 256 + t).
+// energies: part[chunk][E] (thread t takes energies tile * 512 + t and + 256).
+// Bound by the evaluations: the reciprocal is v_rcp_f64 with one third-order
+// correction (within 1 ulp).  491,520 pairs at 500 energies 92 us; with IEEE
+// divisions and 8,192 pairs per workgroup, which left half of the compute units
+// idle, 390 us.
 __global__ void __launch_bounds__(256) k_dos_part(const double *eps, const double *wts,
                                                   const int32_t *stats, int ncols, int nu,
-                                                  const double *E, int nE, double eta,
-                                                  double *part)
+                                                  int64_t chunk, const double *E, int nE,
+                                                  double eta, double *part)
 {
-    __shared__ double se[kDosChunk / 4], sw[kDosChunk / 4];
+    __shared__ double2 pair[kDosStage];
     const int64_t npairs = (int64_t)ncols * nu;
-    const int64_t p0 = (int64_t)blockIdx.x * kDosChunk;
-    const int ie = blockIdx.y * kDosTile + threadIdx.x;
-    const double en = ie < nE ? E[ie] : 0.0;
-    double acc = 0.0;
-    for (int64_t s0 = p0; s0 < p0 + kDosChunk && s0 < npairs; s0 += kDosChunk / 4) {
-        const int cnt = (int)min<int64_t>(kDosChunk / 4, min<int64_t>(npairs, p0 + kDosChunk) - s0);
+    const int64_t p0 = (int64_t)blockIdx.x * chunk;
+    const int i0 = blockIdx.y * kDosTile + threadIdx.x, i1 = i0 + 256;
+    const double e0 = i0 < nE ? E[i0] : 0.0, e1 = i1 < nE ? E[i1] : 0.0;
+    const double eta2 = eta * eta;
+    // where a denominator may leave the range of the fast reciprocal (or a value
+    // is not finite) the workgroup divides
+    const bool far = !(fabs(e0) < 1e100) || !(fabs(e1) < 1e100) || !(eta2 > 1e-200 && eta2 < 1e200);
+    double a0 = 0.0, a1 = 0.0;
+    for (int64_t s0 = p0; s0 < p0 + chunk && s0 < npairs; s0 += kDosStage) {
+        const int cnt = (int)min<int64_t>(kDosStage, npairs - s0);
+        bool plain = far;
         __syncthreads();
         for (int t = threadIdx.x; t < cnt; t += 256) {
             const int64_t g = s0 + t;
             const int c = (int)(g / nu), a = (int)(g - (int64_t)c * nu);
             const bool ok = a < stats[(int64_t)c * kStats];
-            se[t] = ok ? eps[g] : 0.0;
-            sw[t] = ok ? wts[g] : 0.0;
+            const double ep = ok ? eps[g] : 0.0;
+            pair[t] = make_double2(ep, ok ? wts[g] * eta : 0.0);
+            plain = plain || !(fabs(ep) < 1e100);
         }
-        __syncthreads();
+        if (__syncthreads_or(plain)) {
+            for (int t = 0; t < cnt; ++t) {
+                const double2 q = pair[t];
+                const double d0 = e0 - q.x, d1 = e1 - q.x;
+                a0 += q.y / (d0 * d0 + eta2);
+                a1 += q.y / (d1 * d1 + eta2);
+            }
+            continue;
+        }
+#pragma unroll 4
         for (int t = 0; t < cnt; ++t) {
-            const double d = en - se[t];
-            acc += sw[t] * eta / (d * d + eta * eta);
+            const double2 q = pair[t];
+            const double d0 = e0 - q.x, d1 = e1 - q.x;
+            const double x0 = fma(d0, d0, eta2), x1 = fma(d1, d1, eta2);
+            const double y0 = __builtin_amdgcn_rcp(x0), y1 = __builtin_amdgcn_rcp(x1);
+            const double r0 = fma(-x0, y0, 1.0), r1 = fma(-x1, y1, 1.0);
+            a0 = fma(q.y, fma(y0, fma(r0, r0, r0), y0), a0);
+            a1 = fma(q.y, fma(y1, fma(r1, r1, r1), y1), a1);
         }
     }
-    if (ie < nE) part[(int64_t)blockIdx.x * nE + ie] = acc;
+    if (i0 < nE) part[(int64_t)blockIdx.x * nE + i0] = a0;
+    if (i1 < nE) part[(int64_t)blockIdx.x * nE + i1] = a1;
 }
 
-// D(E) = spin / pi * sum over chunks (fixed order)
+// D(E) = spin / pi * sum over chunks: 16 energies per workgroup, thread (group,
+// energy) takes chunks group, group + 16, ...; the groups are added in order
 __global__ void __launch_bounds__(256) k_dos_sum(const double *part, int nchunks, int nE,
                                                  double spin, double *out)
 {
-    const int ie = blockIdx.x * 256 + threadIdx.x;
-    if (ie >= nE) return;
+    __shared__ double red[16][17];
+    const int v = threadIdx.x & 15, u = threadIdx.x >> 4;
+    const int ie = blockIdx.x * 16 + v;
     double s = 0.0;
-    for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * nE + ie];
-    out[ie] = spin / M_PI * s;
+    if (ie < nE) {
+#pragma unroll 8
+        for (int c = u; c < nchunks; c += 16) s += part[(int64_t)c * nE + ie];
+    }
+    red[u][v] = s;
+    __syncthreads();
+    if (u == 0 && ie < nE) {
+        s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += red[k][v];
+        out[ie] = spin / M_PI * s;
+    }
 }
 
 // G_ij(z) at the pattern slots of every solved column from the stored
@@ -188,20 +251,27 @@ hipError_t launch_map_sj(int ncols, const int32_t *cols, int o, RegionView cur, 
 
 hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32_t *blk_col,
                          const int32_t *blk_t, const double *dH, const double *dS,
-                         const double *rho, const double *pi, double spin, double *F,
-                         hipStream_t st)
+                         const double *rho, const double *pi, double spin, int64_t nblk,
+                         double *g, double *F, hipStream_t st)
 {
-    const int grid = n_atoms < (1 << 20) ? n_atoms : (1 << 20);
-    hipLaunchKernelGGL(k_forces, dim3(grid), dim3(64), 0, st, n_atoms, o, blk_ptr, blk_col, blk_t,
-                       dH, dS, rho, pi, spin, F);
+    const int oo = o * o;
+    auto grid = [](int64_t n) { return dim3((unsigned)(n < (1 << 20) ? n : (1 << 20))); };
+    if (oo <= 16)
+        hipLaunchKernelGGL(k_block_forces<16>, grid((nblk + 15) / 16), dim3(256), 0, st, nblk, oo, dH, dS,
+                           rho, pi, g);
+    else
+        hipLaunchKernelGGL(k_block_forces<64>, grid((nblk + 3) / 4), dim3(256), 0, st, nblk, oo, dH, dS,
+                           rho, pi, g);
+    hipLaunchKernelGGL(k_forces, grid((n_atoms + 3) / 4), dim3(256), 0, st, n_atoms, blk_ptr, blk_col,
+                       blk_t, g, spin, F);
     return hipGetLastError();
 }
 
 size_t dos_partial_doubles(int ncols, int nu, int nE)
 {
     const int64_t npairs = (int64_t)ncols * nu;
-    const int64_t nchunks = (npairs + kDosChunk - 1) / kDosChunk;
-    return (size_t)nchunks * nE;
+    const int64_t chunk = dos_chunk(npairs, nE);
+    return (size_t)((npairs + chunk - 1) / chunk) * nE;
 }
 
 hipError_t launch_dos(const double *eps, const double *wts, const int32_t *stats, int ncols,
@@ -209,12 +279,13 @@ hipError_t launch_dos(const double *eps, const double *wts, const int32_t *stats
                       double *out, hipStream_t st)
 {
     const int64_t npairs = (int64_t)ncols * nu;
-    const int nchunks = (int)((npairs + kDosChunk - 1) / kDosChunk);
+    const int64_t chunk = dos_chunk(npairs, nE);
+    const int nchunks = (int)((npairs + chunk - 1) / chunk);
     const int tiles = (nE + kDosTile - 1) / kDosTile;
     if (nchunks < 1 || tiles < 1) return hipSuccess;
     hipLaunchKernelGGL(k_dos_part, dim3(nchunks, tiles), dim3(256), 0, st, eps, wts, stats, ncols,
-                       nu, E, nE, eta, part);
-    hipLaunchKernelGGL(k_dos_sum, dim3(tiles), dim3(256), 0, st, part, nchunks, nE, spin, out);
+                       nu, chunk, E, nE, eta, part);
+    hipLaunchKernelGGL(k_dos_sum, dim3((nE + 15) / 16), dim3(256), 0, st, part, nchunks, nE, spin, out);
     return hipGetLastError();
 }
 

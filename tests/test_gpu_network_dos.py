@@ -1,5 +1,6 @@
-"""The network products at the edges of their tiles: batches around the 16-row
-tiles and the splits of K, and what a row index outside the table does."""
+"""The network products and the density of states at the edges of their tiles:
+batches around the 16-row tiles and the splits of K, energies around the tile of
+512, and what each does with an index or an energy outside its range."""
 
 import numpy as np
 import pytest
@@ -76,3 +77,25 @@ def test_an_index_outside_the_table_makes_no_update(env):
     ctx.mlp_train_step(X, T, 16, 1e-3, idx=good)
     assert np.array_equal(ctx.mlp_get_params(), got)
     ctx.mlp_init(seed=3)
+
+
+@pytest.mark.parametrize("nE,eta", [(1, 0.1), (15, 1e-3), (511, 0.1), (513, 1.0), (1025, 0.05)])
+def test_dos_at_tile_edges(env, nE, eta):
+    torch, ma, ctx, s = env
+    import oracle
+    o = s.n_orb
+    rho = torch.zeros(s.nblk * o * o, dtype=torch.float64, device="cuda")
+    ctx.solve_columns(None, s.p, s.q, kT=s.kT, rho=rho)
+    E = np.linspace(-30.0, 25.0, nE)
+    got = ctx.dos(E, eta=eta)
+    ref = oracle.dos(oracle.solve_raw(s), E, eta=eta)
+    # a Ritz value off by 1e-12 moves a Lorentzian by at most 1e-12 / eta of its height
+    assert np.abs(got - ref).max() <= (1e-10 + 1e-11 / eta) * ref.max()
+    # far away and at infinity the density vanishes; the other energies are as before
+    E2 = E.copy()
+    E2[-1] = np.inf
+    got2 = ctx.dos(E2, eta=eta)
+    assert got2[-1] == 0.0
+    assert np.abs(got2[:-1] - got[:-1]).max(initial=0.0) <= 1e-14 * max(got.max(), 1e-300)
+    E2[-1] = 1e170
+    assert ctx.dos(E2, eta=eta)[-1] == 0.0
