@@ -133,7 +133,10 @@ typedef struct {
     int32_t basis_kernel;   /* MA_BASIS_AUTO: the autotuned kernel for (p, q, precision)
                                if ma_autotune ran, else MA_BASIS_ONCHIP in its register
                                form (MA_PREC_FP64, o = 4, regions of at most 512
-                               orbitals, p + q <= 32), else MA_BASIS_WORKSPACE.
+                               orbitals, p + q <= 32); MA_BASIS_ATOM (MA_PREC_FP64,
+                               o = 9, at least as many atoms as compute units and on
+                               average 7 columns of each, and its workspaces fit);
+                               else MA_BASIS_WORKSPACE.
                                MA_BASIS_WORKSPACE: one column per workgroup, basis in a
                                device workspace, one dot sweep and one update sweep per
                                basis vector.
@@ -160,7 +163,8 @@ typedef struct {
                                chunk buffers of at most 8 GiB; 0 or 1: off (chunks in
                                sequence on one stream); -1 (default): the autotuned
                                choice for (p, q, precision) if ma_autotune ran, else 4
-                               (0 where the automatic kernel is MA_BASIS_ONCHIP) */
+                               (0 where the kernel is MA_BASIS_ATOM or the automatic
+                               one is MA_BASIS_ONCHIP) */
     int32_t keep_sj;        /* 1: keep each solved column's s_j = S_A^-1 e_j (region
                                vector, FP64, M * nmax doubles in all) for a later solve
                                with MA_START_PREVIOUS; the kept set belongs to the

@@ -968,10 +968,12 @@ struct BufSource {
 ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, int32_t q,
                     double mu, double kT, const ma_opts *opts_in, double *rho, double *pi,
                     double *eps, double *wts, int32_t *col_stats, float *sj_near,
-                    int slots_override, int sched_override, Plan &P, BufSource *src = nullptr)
+                    int slots_override, int sched_override, Plan &P, BufSource *src = nullptr,
+                    bool auto_atom = true)
 {
     BufSource own;
     if (!src) src = &own;
+    const size_t src_off = src->off;
     if (!ctx->built) return ctx->fail(MA_ESTATE, "ma_build_system has not succeeded");
     ma_default_opts(&P.opts);
     if (opts_in) P.opts = *opts_in;
@@ -1037,6 +1039,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         return ctx->fail(MA_EINVAL, "unknown basis kernel %d", opts.basis_kernel);
     if (opts.chunk_columns < 0) return ctx->fail(MA_EINVAL, "chunk_columns must be >= 0");
     if (opts.pipeline < -1) return ctx->fail(MA_EINVAL, "pipeline must be >= -1");
+    const int o = ctx->o;
     const bool fits = ma::basis_small_fits(ctx->nmax, P.nu, q, ctx->o);
     const bool gfits = ma::basis_group_fits(ctx->nmax, P.nu, ctx->o);
     const bool afits = ma::basis_atom_fits(ctx->nmax, P.nu, ctx->o, opts.precision);
@@ -1059,12 +1062,35 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     const bool resident = (want_kernel == MA_BASIS_AUTO || (want_kernel == MA_BASIS_ONCHIP && fits)) &&
                           ma::basis_resident_fits(ctx->nmax, P.nu, q, ctx->o, opts.precision,
                                                   ma::lidx_bytes(ctx->max_nat, (int)ctx->max_lnnz));
-    if (want_kernel == MA_BASIS_AUTO) want_kernel = MA_BASIS_WORKSPACE;
-    // The resident kernel's workgroups take every register of their compute
-    // unit, so that no eigensolver runs beside them: chunks in sequence (4,096
-    // sp3 atoms 16.8 ms, pipelined 17.3 ms).
-    const int pipe = opts.pipeline >= 0 ? opts.pipeline
-                     : tn && tn->pipe >= 0 ? tn->pipe : resident ? 0 : 4;
+    // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of 630
+    // orbitals, nu = 30: 23.6 ms against 42.2 (1.5 to 2.6 times at 500 to 864
+    // atoms and nu = 1 to 48).  It runs one workgroup per atom, so it needs the
+    // atoms to fill the chip (256 atoms: 16.2 against 20.1 ms) and most columns
+    // of each (7 of 9: 1.1 to 1.6 times, 5 of 9: 0.9 to 1.4, 2 of 9: 0.5 to 0.8).
+    // For o = 4 the workspace kernel is faster (3,001 atoms of up to 1,040
+    // orbitals, nu = 40: 35 ms against 57).
+    auto_atom = auto_atom && want_kernel == MA_BASIS_AUTO && !resident && afits && o == 9 &&
+                opts.precision == MA_PREC_FP64 && ncols >= 7 * (int64_t)ctx->cu_count;
+    if (auto_atom) {
+        std::vector<char> seen(ctx->n_atoms, 0);
+        int64_t atoms = 0;
+        for (int64_t c = 0; c < ncols; ++c) {
+            char &a = seen[P.hcols[c] / o];
+            atoms += !a;
+            a = 1;
+        }
+        auto_atom = atoms >= ctx->cu_count && ncols >= 7 * atoms;
+    }
+    if (want_kernel == MA_BASIS_AUTO) want_kernel = auto_atom ? MA_BASIS_ATOM : MA_BASIS_WORKSPACE;
+    // (its workgroups' workspaces are larger: where they do not fit, the plan
+    // is made again with the workspace kernel)
+    auto without_atom = [&] {
+        (void)hipGetLastError();
+        src->off = src_off;
+        P = Plan();
+        return make_plan(ctx, ncols, cols, p, q, mu, kT, opts_in, rho, pi, eps, wts, col_stats, sj_near,
+                         slots_override, sched_override, P, src, false);
+    };
     // the group kernel neither starts from nor keeps whole-region s_j
     const bool sj_io = opts.start == MA_START_PREVIOUS || opts.keep_sj;
     if (opts.basis_kernel == MA_BASIS_GROUP && sj_io)
@@ -1072,11 +1098,16 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     if ((want_kernel == MA_BASIS_ONCHIP && !fits) || (want_kernel == MA_BASIS_GROUP && !gfits) ||
         (want_kernel == MA_BASIS_ATOM && !afits) || (want_kernel == MA_BASIS_GROUP && sj_io))
         want_kernel = MA_BASIS_WORKSPACE;
+    // The resident kernel's workgroups take every register of their compute
+    // unit, so that no eigensolver runs beside them: chunks in sequence (4,096
+    // sp3 atoms 16.8 ms, pipelined 17.3 ms).  Beside the atom kernel one costs
+    // more than it hides (2,048 spd atoms, nu = 30, FP64: 97 ms, pipelined 159).
+    const int pipe = opts.pipeline >= 0 ? opts.pipeline
+                     : tn && tn->pipe >= 0 ? tn->pipe : resident || want_kernel == MA_BASIS_ATOM ? 0 : 4;
     P.kind = resident ? ma::kBasisResident
              : want_kernel == MA_BASIS_ONCHIP ? ma::kBasisOnchip
              : want_kernel == MA_BASIS_GROUP ? ma::kBasisGroup
              : want_kernel == MA_BASIS_ATOM ? ma::kBasisAtom : ma::kBasisWorkspace;
-    const int o = ctx->o;
     J.lidx = P.kind == ma::kBasisResident ? 1
              : P.kind == ma::kBasisWorkspace ? S.lidx
              : P.kind == ma::kBasisOnchip
@@ -1298,6 +1329,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
                 // as many persistent workgroups as the rest of the region holds
                 const size_t used = (src->off + 255) & ~(size_t)255;
                 const int64_t fit = used < src->cap ? (int64_t)((src->cap - used) / slot_bytes) : 0;
+                if (auto_atom && fit < P.slots) return without_atom();
                 if (fit < 1)
                     return ctx->fail(MA_EINVAL, "the solve needs more than the %zu-byte scratch "
                                      "(%zu bytes before the first basis workspace of %zu bytes)",
@@ -1308,6 +1340,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         }
         P.bytes = (src->off + 255) & ~(size_t)255;
         if (src->size_only) return MA_OK;
+        if (src->off > src->cap && auto_atom) return without_atom();
         if (src->off > src->cap)
             return ctx->fail(MA_EINVAL, "the solve needs %zu bytes of workspace, %zu given",
                              src->off, src->cap);
@@ -1316,6 +1349,11 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         HIPCHK(ctx, ctx->order.reserve(n_order), "order");
         HIPCHK(ctx, ctx->qbounds.reserve(n_qb), "queues");
         HIPCHK(ctx, ctx->gstart.reserve(n_gstart), "work items");
+        if (auto_atom && slot_bytes * P.slots > ctx->ws.bytes) {
+            size_t fr = 0, tot = 0;
+            if (hipMemGetInfo(&fr, &tot) != hipSuccess || slot_bytes * P.slots > (fr + ctx->ws.bytes) / 2)
+                return without_atom();
+        }
         if (slot_bytes) HIPCHK(ctx, ctx->ws.reserve(slot_bytes * P.slots), "workspace");
         HIPCHK(ctx, ctx->mid.reserve(n_mid), "chunk buffer");
         if (n_eps) HIPCHK(ctx, ctx->eps.reserve(n_eps), "eps");
