@@ -2389,6 +2389,7 @@ __global__ void __launch_bounds__(256) k_minmax(const double *eps, const int32_t
     if (threadIdx.x == 0) {
         lohi[0] = lo - 50.0 * kT;
         lohi[1] = hi + 50.0 * kT;
+        lohi[2] = 0.0;
         count_state(part)[0] = count_state(part)[1] = 0;
     }
 }
@@ -2404,11 +2405,11 @@ __global__ void __launch_bounds__(256) k_minmax(const double *eps, const int32_t
 // order kSeries are below (1 / 16 pi)^{kSeries+1} = 2e-17 of the weight (the
 // poles of f lie at distance pi).  One pass sums the coefficients over the Ritz
 // pairs, the rest of the kBisectPasses K-section steps run on the polynomial,
-// and the passes that are left return at once.
+// and the passes that are left return at once; lohi[2] counts the steps done.
 // Every block writes its partial sums; the last to finish adds them in a fixed
 // order.  A pass is a chain of latencies (two reductions, a counter).  The whole
 // search on 4,096, 491,520 and 1,866,240 Ritz pairs with kT = 0.1 to 0.2 eV (three
-// K-section steps, the series, ten empty passes): 79, 149 and 329 us; as
+// K-section steps, the series, two empty passes): 43, 110 and 290 us; as
 // kBisectPasses K-section steps 262, 800 and 2,120 us.
 constexpr int kSeries = 9;
 
@@ -2505,6 +2506,7 @@ __global__ void __launch_bounds__(256) k_count(const double *eps, const double *
     if (lane == 0) {
         lohi[0] = l;
         lohi[1] = h;
+        lohi[2] = done;
         state[1] = done;
     }
 }

@@ -11,6 +11,7 @@ constexpr int kThreads = 256;            // workgroup size of the column kernel
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxNu = 64;
 constexpr int kBisectTrials = 15;        // trial potentials per bisection pass
+constexpr int kFirstPasses = 6;          // launched at once: a bracket of 16^5 kT / 8 narrows below kT / 8
 constexpr int kBisectPasses = 14;        // 16^14 = 7.2e16: any bracket narrows below 1e-15
 constexpr int kCountBlocks = 1024;       // fixed grid of the electron-count kernel
 constexpr int kNbDesc = 48;              // neighbours in a column descriptor
@@ -152,7 +153,7 @@ hipError_t launch_minmax(const double *eps, const int32_t *stats, int ncols, int
                          double kT, double *lohi, double *partial, int *counter, hipStream_t st);
 hipError_t launch_bisect(const double *eps, const double *wts, const int32_t *stats,
                          int ncols, int nu, double kT, double n_target, double *lohi,
-                         double *partial, hipStream_t st);
+                         double *partial, int passes, hipStream_t st);
 hipError_t launch_rho(const DevSystem &S, const DevJob &J, const double *mu_ptr, double kT,
                       double *rho, double *pi, double *Ecol, double *Ncol, hipStream_t st);
 hipError_t launch_sum2(const double *a, const double *b, int n, double *out, hipStream_t st);

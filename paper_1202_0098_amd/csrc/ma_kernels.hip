@@ -213,10 +213,10 @@ hipError_t launch_minmax(const double *eps, const int32_t *stats, int ncols, int
 
 hipError_t launch_bisect(const double *eps, const double *wts, const int32_t *stats, int ncols,
                          int nu, double kT, double n_target, double *lohi, double *partial,
-                         hipStream_t st)
+                         int passes, hipStream_t st)
 {
     const int grid = count_grid(ncols, nu);
-    for (int pass = 0; pass < kBisectPasses; ++pass)
+    for (int pass = 0; pass < passes; ++pass)
         hipLaunchKernelGGL(k_count, dim3(grid), dim3(256), 0, st, eps, wts, stats, ncols, nu, kT,
                            n_target, lohi, partial);
     return hipGetLastError();

@@ -54,3 +54,30 @@ def test_mu(kT, fill):
     ctx.find_mu(target, 2 * kT)
     assert ctx.find_mu(target, kT).mu == r.mu
     ctx.close()
+
+
+@pytest.mark.parametrize("kT", [1e-7, 1e-5, 0.1])
+def test_density_at_the_found_mu(kT):
+    """The density and the sums belong to the mu that is returned, also where the
+    search needs more passes than are launched at once (small kT)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    s = synth.config_diamond64()
+    o = s.n_orb
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    rho, again, ref = (torch.zeros(s.nblk * o * o, dtype=torch.float64, device="cuda") for _ in range(3))
+    # a filling at which no level is partly occupied: mu lies in a gap
+    r = ctx.solve_columns(None, s.p, s.q, kT=kT, rho=rho)
+    f = ctx.find_mu(0.5 * s.M, kT, rho=again)
+    g = ctx.solve_columns(None, s.p, s.q, mu=r.mu, kT=kT, rho=ref)
+    torch.cuda.synchronize()
+    # an occupation moves by at most dmu / 4 kT; mu is exact to a few ulp of 1 eV
+    tol = 1e-10 + 1e-15 / kT
+    print(f"[gpu-case] kT={kT}: d rho {float((rho - ref).abs().max()):.1e} dN {abs(r.n_elec - g.n_elec):.1e}", flush=True)
+    assert float((rho - ref).abs().max()) <= tol
+    assert abs(r.n_elec - g.n_elec) <= tol * s.M and abs(r.energy - g.energy) <= tol * s.M * 10
+    assert f.mu == r.mu and float((again - ref).abs().max()) <= tol
+    ctx.close()
