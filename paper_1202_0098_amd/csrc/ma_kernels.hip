@@ -226,15 +226,19 @@ hipError_t launch_rho(const DevSystem &S, const DevJob &J, const double *mu_ptr,
                       double *rho, double *pi, double *Ecol, double *Ncol, hipStream_t st)
 {
     const int grid = J.ncols < 65536 ? J.ncols : 65536;
-    const size_t blk = (size_t)S.maxpat * J.nu * (J.precision == 0 ? sizeof(double) : sizeof(float));
-    const int stage = blk <= 48 * 1024 ? 1 : 0;
-    const size_t smem = stage ? blk : 0;
-    if (J.precision == 0)
-        hipLaunchKernelGGL(k_rho<double>, dim3(grid), dim3(128), smem, st, S, J, mu_ptr, kT, rho,
-                           pi, Ecol, Ncol, stage);
-    else
-        hipLaunchKernelGGL(k_rho<float>, dim3(grid), dim3(128), smem, st, S, J, mu_ptr, kT, rho,
-                           pi, Ecol, Ncol, stage);
+    // rows of amplitudes per stage: 128 (one per pair of lanes) while they fit
+    // 32 KB, which leaves room for five workgroups on a compute unit
+    const size_t row = J.nu * (J.precision == 0 ? sizeof(double) : sizeof(float));
+    const int rows = (int)std::min<size_t>(std::min(128, S.maxpat), std::max<size_t>(1, 32 * 1024 / row));
+    // one wavefront per column where a pass of it holds the rows (16,384 columns
+    // of 20 rows: 26 us, 68 with four)
+    using Fn = void (*)(DevSystem, DevJob, const double *, double, double *, double *, double *, double *,
+                        int);
+    const int nt = S.maxpat <= 32 ? 64 : 256;
+    const Fn fn = J.precision == 0 ? (nt == 64 ? k_rho<double, 64> : k_rho<double, 256>)
+                                   : (nt == 64 ? k_rho<float, 64> : k_rho<float, 256>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(nt), rows * row, st, S, J, mu_ptr, kT, rho, pi, Ecol, Ncol,
+                       rows);
     return hipGetLastError();
 }
 

@@ -81,3 +81,35 @@ def test_density_at_the_found_mu(kT):
     assert abs(r.n_elec - g.n_elec) <= tol * s.M and abs(r.energy - g.energy) <= tol * s.M * 10
     assert f.mu == r.mu and float((again - ref).abs().max()) <= tol
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["sp3", "spd"])
+@pytest.mark.parametrize("precision,p,q", [("fp64", 1, 0), ("fp64", 2, 1), ("fp64", 15, 15),
+                                           ("fp64", 32, 32), ("mixed_f64acc", 9, 8)])
+def test_stored_amplitudes_give_the_density_of_a_given_mu(kind, precision, p, q):
+    """rho and pi of a bisected solve (amplitudes stored, then weighted) against
+    the same columns at that mu (weighted before they are stored): 20 and up to
+    390 rows, stages of 128, 64 and fewer rows."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    s = synth.config_diamond64() if kind == "sp3" else synth.config_fcc_spd(5, cells=(4, 4, 4))
+    cols = np.arange(0, s.M, 1 if kind == "sp3" else 7, dtype=np.int32)
+    o = s.n_orb
+    print(f"[gpu-case] {kind} {precision} p={p} q={q}", flush=True)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    out = [torch.zeros(s.nblk * o * o, dtype=torch.float64, device="cuda") for _ in range(4)]
+    opts = ma.default_opts(precision=precision)
+    r = ctx.solve_columns(cols, p, q, kT=s.kT, rho=out[0], pi=out[1], opts=opts)
+    g = ctx.solve_columns(cols, p, q, mu=r.mu, kT=s.kT, rho=out[2], pi=out[3], opts=opts)
+    torch.cuda.synchronize()
+    # FP64: rounding of sums of at most 64 terms of order one (eps up to 30 for
+    # pi); FP32 amplitudes: an ulp of each, 64 * 6e-8
+    tol = 1e-10 if precision == "fp64" else 4e-6
+    assert float((out[0] - out[2]).abs().max()) <= tol
+    assert float((out[1] - out[3]).abs().max()) <= 30 * tol
+    assert abs(r.energy - g.energy) <= 30 * tol * len(cols)
+    assert abs(r.n_elec - g.n_elec) <= tol * len(cols)
+    ctx.close()
