@@ -6,10 +6,10 @@ namespace ma {
 
 namespace {
 
-// One column of the chunk per workgroup of CW * NG threads (nu <= CW).  Thread
-// t holds, for column t % CW, the rows (t / CW) * CW / NG + r of every nu x nu
-// matrix in registers, so that each step of the factorisations is one rank-two
-// update of CW / NG rows per thread against two vectors that go through LDS:
+// One column of the chunk per workgroup of CW * NG threads (nu <= RM <= CW).
+// Thread t holds, for column t % CW, the rows (t / CW) * RM / NG + r of every
+// nu x nu matrix in registers, so that each step of the factorisations is one
+// rank-two update of RM / NG rows per thread against two vectors that go through LDS:
 //   congruence  A = Lc^-1 H~ Lc^-T and G = Lc^-T together, one column of the
 //               Cholesky factor of S~ = Lc Lc^T per step;
 //   Householder A = Q T Q^T with G Q accumulated from the left;
@@ -31,11 +31,12 @@ namespace {
 // one of nu = 16 75 us (189 us).
 constexpr int kEigWaves = 3;   // waves per SIMD that the registers leave room for
 
-template <int CW, int NG>
+template <int CW, int NG, int RM>
 __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob J)
 {
-    constexpr int RPG = CW / NG, NT = CW * NG, NWV = NT / 64, LDZ = CW + 1;
-    static_assert(RPG % 2 == 0 && (NT == 64 || CW == 64), "one wavefront, or one per row group");
+    constexpr int RPG = RM / NG, NT = CW * NG, NWV = NT / 64, LDZ = RM + 1;
+    static_assert(RPG % 2 == 0 && RM % 16 == 0 && RM <= CW && (NT == 64 || CW == 64),
+                  "one wavefront, or one per row group");
     // columns of C, LDZ apart, and (d, e) of T, each after one entry that a
     // sweep's last prefetch reads
     __shared__ double Zm[(CW + 1) * LDZ];
@@ -89,6 +90,8 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
         G[r] = i == col ? 1.0 : 0.0;
     }
 
+    // the columns past the rows are zero throughout
+    if (RM < CW && tid >= RM && tid < CW) xs[tid] = ys[tid] = gs[tid] = 0.0;
     // Congruence.  With l the column k of the Cholesky factor (l_k set to
     // lk - 1) and a = A e_k / lk, b = a - (alpha / 2) l:
     // A -= l b^T + b l^T and G -= g l^T scale and eliminate row and column
@@ -183,7 +186,7 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
     for (int r = 0; r < RPG; ++r) {
         diag = row0 + r == col ? A[r] : diag;
         last = row0 + r == L - 1 ? A[r] : last;
-        Z[(row0 + r) * LDZ + col] = G[r];
+        if (RM == CW || col < RM) Z[(row0 + r) * LDZ + col] = G[r];
     }
     if (col >= row0 && col < row0 + RPG) de[col].x = diag;
     if (col == L - 2 && L - 1 >= row0 && L - 1 < row0 + RPG) de[col].y = last;
@@ -200,10 +203,10 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
     // and (i - 1, i); d, e and the column of the next rotation are read
     // one rotation ahead.  The loop is one wavefront's instruction issue
     // (about 45 per rotation), so it has no branch inside: f = g = 0 takes
-    // the identity as its rotation, the lanes past CW repeat rows, and d, e
+    // the identity as its rotation, the lanes past the rows repeat some, and d, e
     // are written by lane 0 while the others write to places of their own.
     if (wv == 0) {
-        const int rl = lane % CW;
+        const int rl = lane % RM;
         const int own = lane == 0 ? 1 : 0;
         for (int l = 0; l < L && status == 0; ++l) {
             int sweeps = 0;
@@ -332,9 +335,9 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
         for (int mt = wv; mt < nrt; mt += NWV) {
             const int arow = mt * 16 + l16;
             // this lane's basis-row operands, loaded together
-            double avs[CW / 4];
+            double avs[RM / 4];
 #pragma unroll
-            for (int k4 = 0; k4 < CW / 4; ++k4) {
+            for (int k4 = 0; k4 < RM / 4; ++k4) {
                 const int kk = 4 * k4 + kq;
                 const bool in = arow < npat && kk < L;
                 const double uv = Up[in ? (2 + arow) * nu + kk : 0];
@@ -344,9 +347,9 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
                 const int bcol = ct * 16 + l16;
                 dbl4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int k4 = 0; k4 < CW / 4; ++k4) {
+                for (int k4 = 0; k4 < RM / 4; ++k4) {
                     const int kk = 4 * k4 + kq;
-                    const double zv = Z[(bcol < CW ? bcol : 0) * LDZ + kk];
+                    const double zv = Z[(bcol < RM ? bcol : 0) * LDZ + kk];
                     const double cv = bcol < L && kk < L ? zv : 0.0;
                     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(avs[k4], cv, acc, 0, 0, 0);
                 }
@@ -779,18 +782,20 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
     }
 }
 
-template <int CW, int NG>
+template <int CW, int NG, int RM = CW>
 hipError_t launch_width(const DevSystem &S, const DevJob &J, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_eig<CW, NG>), dim3(J.cn), dim3(CW * NG), 0, st, S, J);
+    hipLaunchKernelGGL((k_eig<CW, NG, RM>), dim3(J.cn), dim3(CW * NG), 0, st, S, J);
     return hipGetLastError();
 }
 
 }  // namespace
 
 // Amplitudes in FP32: k_eig_f32.  Otherwise the smallest width that holds nu:
-// one wavefront per column up to 32 (16 columns x 4 row groups, 32 x 2),
-// beyond that four wavefronts with a barrier per step.
+// one wavefront per column up to 32 (16 columns x 4 row groups, 32 x 2), two
+// with 24 rows each up to 48 (12,004 columns of nu = 40: 5.7 ms, 7.0 with the four
+// below: what every wavefront does for itself in a step, about 100 instructions,
+// weighs as much as its rows), beyond that four with 16 rows each.
 hipError_t launch_eig(const DevSystem &S, const DevJob &J, hipStream_t st)
 {
     if (J.cn < 1) return hipSuccess;
@@ -806,6 +811,7 @@ hipError_t launch_eig(const DevSystem &S, const DevJob &J, hipStream_t st)
     }
     if (J.nu <= 16) return launch_width<16, 4>(S, J, st);
     if (J.nu <= 32) return launch_width<32, 2>(S, J, st);
+    if (J.nu <= 48) return launch_width<64, 2, 48>(S, J, st);
     return launch_width<64, 4>(S, J, st);
 }
 

@@ -1,4 +1,4 @@
-"""The reduced eigenproblem at the edges of its kernels' widths (16, 32 and 64
+"""The reduced eigenproblem at the edges of its kernels' widths (16, 32, 48 and 64
 columns; nu = 1 and 2, where no reduction to tridiagonal form is needed), with
 given and with bisected chemical potential.
 
@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("p,q", [(1, 0), (1, 1), (2, 1), (8, 7), (8, 8), (9, 8), (16, 15), (16, 16),
-                                 (17, 16), (25, 20), (63, 0), (64, 0)])
+                                 (17, 16), (25, 20), (47, 0), (48, 0), (49, 0), (63, 0), (64, 0)])
 @pytest.mark.parametrize("bisect", [False, True])
 def test_widths(p, q, bisect):
     torch = pytest.importorskip("torch")
