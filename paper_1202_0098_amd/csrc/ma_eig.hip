@@ -453,6 +453,10 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
         int32_t *st = J.stats + (int64_t)c * kStats;
         int L = st[3] == 0 ? st[0] : 0;
         int status = 0;
+        // up to 32 columns: two lanes per column, which take turns along its rows
+        // in the updates (a sum of products stays one lane's)
+        const bool two = L <= 32;
+        const int c0 = two ? lane & 31 : lane, r0 = two ? lane >> 5 : 0, dr = two ? 2 : 1;
 #pragma unroll 4
         for (int e = lane; e < L * L; e += 64) {
             const int i = e / L, k = e - i * L;
@@ -476,10 +480,11 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
             const double lk = sqrt(dk), rl = 1.0 / lk;
             for (int i = k + 1 + lane; i < L; i += 64) B[i * L + k] *= rl;
             __syncthreads();
-            for (int j = k + 1 + lane; j < L; j += 64) {
+            const int j = k + 1 + c0;
+            if (j < L) {
                 const double bjk = B[j * L + k];
                 #pragma unroll 4
-                for (int i = j; i < L; ++i) B[i * L + j] -= B[i * L + k] * bjk;
+                for (int i = j + r0; i < L; i += dr) B[i * L + j] -= B[i * L + k] * bjk;
             }
             if (lane == 0) {
                 B[k * L + k] = lk;
@@ -490,13 +495,15 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
         // A = Lc^-1 H~ Lc^-T in place: W = Lc^-1 A (a lane per column), then
         // A = Lc^-1 W^T
         for (int pass = 0; pass < 2; ++pass) {
-            for (int k = 0; k < L; ++k)
-                for (int cc = lane; cc < L; cc += 64) {
-                    const double ak = A[k * L + cc] * rd[k];
-                    A[k * L + cc] = ak;
+            for (int k = 0; k < L; ++k) {
+                if (c0 < L) {
+                    const double ak = A[k * L + c0] * rd[k];
                     #pragma unroll 4
-                    for (int i = k + 1; i < L; ++i) A[i * L + cc] -= B[i * L + k] * ak;
+                    for (int i = k + 1 + r0; i < L; i += dr) A[i * L + c0] -= B[i * L + k] * ak;
+                    if (r0 == 0) A[k * L + c0] = ak;
                 }
+                wave_sync();
+            }
             __syncthreads();
             if (pass == 0) {
                 for (int e = lane; e < L * L; e += 64) {
@@ -564,10 +571,13 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
                 if (j < L) hq[j] = qj;
                 __syncthreads();
                 // A' -= v q^T + q v^T
-                if (j < L)
+                const int jc = k + 1 + c0;
+                if (jc < L) {
+                    const double qc = hq[jc], vc = hv[jc];
                     #pragma unroll 4
-                    for (int ii = k + 1; ii < L; ++ii)
-                        A[ii * L + j] -= hv[ii] * qj + hq[ii] * vjj;
+                    for (int ii = k + 1 + r0; ii < L; ii += dr)
+                        A[ii * L + jc] -= hv[ii] * qc + hq[ii] * vc;
+                }
             }
             __syncthreads();
         }
@@ -581,14 +591,16 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
         for (int k = L - 3; k >= 0; --k) {
             const double h = hh[k];
             if (!(h > 0.0)) continue;
-            for (int cc = k + 1 + lane; cc < L; cc += 64) {
+            const int cc = k + 1 + c0;
+            if (cc < L) {
                 double t = 0.0;
                 #pragma unroll 4
                 for (int i = k + 1; i < L; ++i) t += A[i * L + k] * Z[cc * L + i];
                 t /= h;
                 #pragma unroll 4
-                for (int i = k + 1; i < L; ++i) Z[cc * L + i] -= A[i * L + k] * t;
+                for (int i = k + 1 + r0; i < L; i += dr) Z[cc * L + i] -= A[i * L + k] * t;
             }
+            wave_sync();
         }
         __syncthreads();
 
@@ -693,13 +705,14 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
         __syncthreads();
         for (int e = lane; e < L * L; e += 64) B[e] = mid[nu * nu + e];
         __syncthreads();
-        for (int a = lane; a < L; a += 64) {
-            for (int k = L - 1; k >= 0; --k) {
-                const double ck = A[k * L + a] * rd[k];
-                A[k * L + a] = ck;
+        for (int k = L - 1; k >= 0; --k) {
+            if (c0 < L) {
+                const double ck = A[k * L + c0] * rd[k];
                 #pragma unroll 4
-                for (int i = 0; i < k; ++i) A[i * L + a] -= B[k * L + i] * ck;
+                for (int i = r0; i < k; i += dr) A[i * L + c0] -= B[k * L + i] * ck;
+                if (r0 == 0) A[k * L + c0] = ck;
             }
+            wave_sync();
         }
         __syncthreads();
         if (status != 0) {
