@@ -428,7 +428,9 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
 //   Householder reduction A = Q T Q^T, Q accumulated backwards; implicit QL;
 //   C = Lc^-T Z.
 // Every lane runs the scalar recurrences of the QL sweeps redundantly, so they
-// need no broadcasts.
+// need no broadcasts.  Bound by instruction issue of the nine wavefronts that LDS
+// lets a compute unit hold: 62,208 columns of nu = 30 17.4 ms; with lanes masked
+// in the rotation loop 20.5, and with one lane per column in the updates too 22.0.
 __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
 {
     extern __shared__ double smem[];
@@ -610,7 +612,11 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
         // up to l.  At most 64 sweeps per eigenvalue.  The rotation loop is
         // software-pipelined: the entries of the next rotation are loaded one
         // rotation ahead, and the rotated column i stays in a register for the
-        // next rotation (columns i + 1 are final once written).
+        // next rotation (columns i + 1 are final once written).  No lane is masked
+        // out: those past the rows repeat row 0, and those that do not keep T write
+        // their entries to the idle Householder vectors.  Which products are
+        // rounded before they are added is written out (p is, by the empty asm).
+        const int rw = lane < L ? lane : 0, own = lane == 0 ? 1 : 0;
         for (int l = 0; l < L && status == 0; ++l) {
             int sweeps = 0;
             for (;;) {
@@ -633,27 +639,23 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
                 double g = dm - dl0 + el / (t0 + (t0 >= 0.0 ? r0 : -r0));
                 double sn = 1.0, cs = 1.0, p = 0.0;
                 bool underflow = false;
-                const bool row = lane < L;
                 double e_i = ee[m - 1], d_i = ev[m - 1], d_i1 = dm;
-                double z_i1 = row ? Z[m * L + lane] : 0.0;
-                double z_i = row ? Z[(m - 1) * L + lane] : 0.0;
+                double *zp = Z + m * L + rw;
+                double z_i1 = zp[0], z_i = zp[-L];
+                double *ep = lane == 0 ? ee + m : hv + lane, *dp = lane == 0 ? ev + m : hq + lane;
                 for (int i = m - 1; i >= l; --i) {
-                    double e_n = 0.0, d_n = 0.0, z_n = 0.0;
-                    if (i > l) {
-                        e_n = ee[i - 1];
-                        d_n = ev[i - 1];
-                        z_n = row ? Z[(i - 1) * L + lane] : 0.0;
-                    }
+                    // (the last prefetch reads one entry below, whatever lies there)
+                    const double e_n = ee[i - 1], d_n = ev[i - 1], z_n = zp[-2 * L];
                     const double f = sn * e_i, b = cs * e_i;
-                    const double r2 = f * f + g * g;
-                    if (r2 == 0.0) {
+                    const double r2 = fma(g, g, f * f);
+                    if (__ballot(r2 == 0.0)) {
                         const double dnew = d_i1 - p;
                         if (lane == 0) {
                             ee[i + 1] = 0.0;
                             ev[i + 1] = dnew;
                             ee[m] = 0.0;
                         }
-                        if (row) Z[(i + 1) * L + lane] = z_i1;
+                        *zp = z_i1;
                         underflow = true;
                         break;
                     }
@@ -661,16 +663,18 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
                     sn = f * ir;
                     cs = g * ir;
                     g = d_i1 - p;
-                    const double rr = (d_i - g) * sn + 2.0 * cs * b;
+                    const double rr = fma(d_i - g, sn, 2.0 * cs * b);
                     p = sn * rr;
-                    if (lane == 0) {
-                        ee[i + 1] = r2 * ir;
-                        ev[i + 1] = g + p;
-                    }
-                    g = cs * rr - b;
-                    const double zn1 = sn * z_i + cs * z_i1;
-                    const double zn0 = cs * z_i - sn * z_i1;
-                    if (row) Z[(i + 1) * L + lane] = zn1;
+                    asm("" : "+v"(p));
+                    *ep = r2 * ir;
+                    *dp = g + p;
+                    ep -= own;
+                    dp -= own;
+                    g = fma(cs, rr, -b);
+                    const double zn1 = fma(sn, z_i, cs * z_i1);
+                    const double zn0 = fma(cs, z_i, -(sn * z_i1));
+                    *zp = zn1;
+                    zp -= L;
                     z_i1 = zn0;
                     z_i = z_n;
                     e_i = e_n;
@@ -678,7 +682,7 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
                     d_i = d_n;
                 }
                 if (underflow) continue;
-                if (row) Z[l * L + lane] = z_i1;
+                *zp = z_i1;
                 if (lane == 0) {
                     ev[l] = dl0 - p;
                     ee[l] = g;

@@ -48,3 +48,29 @@ def test_widths(p, q, bisect):
     assert np.abs(got[1] - oracle.scatter_slots(s, cols, pi_o)).max() <= 1e-10 * np.abs(pi_o).max()
     assert abs(r.energy - 2 * E.sum()) <= 1e-10 * abs(E).sum()
     ctx.close()
+
+
+@pytest.mark.parametrize("nu", [1, 2, 3, 31, 32, 33, 64])
+def test_stored_fp32_amplitudes(nu):
+    """The kernel of the mixed modes with mu bisected (two lanes per column up to
+    32 columns).  The operator is rounded to FP32: 6e-8 of a norm of about 10
+    moves an occupation by 6e-7 / 4 kT and a Ritz value by 6e-7; an order of
+    magnitude for the subspace."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle
+    import paper_1202_0098_amd as ma
+    s = synth.random_pencil(24, 4, seed=31)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    cols = np.arange(5, 29, dtype=np.int32)
+    print(f"[gpu-case] pencil n={s.M} nu={nu} mixed_f64acc", flush=True)
+    rho = torch.zeros(s.nblk * 16, dtype=torch.float64, device="cuda")
+    r = ctx.solve_columns(cols, nu, 0, kT=0.25, rho=rho,
+                          opts=ma.default_opts(n_target=12.0, precision="mixed_f64acc"))
+    raw = oracle.solve_raw(s, cols=cols, p=nu, q=0)
+    rho_o = oracle.outputs(s, raw, r.mu, 0.25)[0]
+    assert abs(r.mu - oracle.find_mu(raw, 0.25, 12.0)) <= 1e-5
+    assert np.abs(rho.cpu().numpy().reshape(s.nblk, 4, 4) - oracle.scatter_slots(s, cols, rho_o)).max() <= 1e-5
+    ctx.close()
