@@ -2195,11 +2195,18 @@ ma_status net_train_core(ma_ctx *ctx, const float *x, const float *t, const int3
     if (idx) HIPCHK(ctx, hipMemcpyAsync(&bad, N.bad.p, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
     double part[256];
     HIPCHK(ctx, hipMemcpyAsync(part, N.partial.p, sizeof part, hipMemcpyDeviceToHost, st), "copy");
-    if (grad_host)
-        HIPCHK(ctx, hipMemcpyAsync(grad_host, g, sizeof(float) * N.P, hipMemcpyDeviceToHost, st), "copy");
+    auto copy_grad = [&] {
+        return hipMemcpyAsync(grad_host, g, sizeof(float) * N.P, hipMemcpyDeviceToHost, st);
+    };
+    if (grad_host && !idx) HIPCHK(ctx, copy_grad(), "copy");
     HIPCHK(ctx, hipStreamSynchronize(st), "training step");
     if (bad) return ctx->fail(MA_EINVAL, "a row index is outside the table of %lld rows",
                               (long long)n_rows);
+    // (a call that fails leaves the caller's gradient as it was)
+    if (grad_host && idx) {
+        HIPCHK(ctx, copy_grad(), "copy");
+        HIPCHK(ctx, hipStreamSynchronize(st), "training step");
+    }
     if (update) {
         N.step += 1;
         N.bf16_dirty = true;

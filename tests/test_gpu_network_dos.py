@@ -2,6 +2,8 @@
 batches around the 16-row tiles and the splits of K, energies around the tile of
 512, and what each does with an index or an energy outside its range."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -70,6 +72,12 @@ def test_an_index_outside_the_table_makes_no_update(env):
         with pytest.raises(Exception, match="outside the table"):
             ctx.mlp_train_step(X, T, 16, 1e-3, idx=idx)
         assert np.array_equal(ctx.mlp_get_params(), before)
+        # nor has a caller's gradient buffer been written by a call that fails
+        g = np.full(sh["n_params"], 3.0, np.float32)
+        loss = ctypes.c_double(5.0)
+        st = ctx._lib.ma_mlp_loss_grad(ctx._h, X.data_ptr(), T.data_ptr(), 20, idx.data_ptr(), 16,
+                                       ctypes.byref(loss), g.ctypes.data)
+        assert st != 0 and loss.value == 5.0 and np.all(g == 3.0)
     # the step counter has not moved either: as from a fresh optimizer
     ctx.mlp_train_step(X, T, 16, 1e-3, idx=good)
     got = ctx.mlp_get_params()
