@@ -146,14 +146,26 @@ __global__ void k_to_bf16_t(const float *W, int rows, int cols, int rows_pad, in
 // B(k,j) = B[k*sb0 + j*sb1]; rows of A optionally gathered through `gather`.
 // If Z != nullptr, Z receives the pre-activation and C = silu(Z); if Zg !=
 // nullptr, C is multiplied by silu'(Zg).
-//
+__device__ __forceinline__ void gemm_store(float r, int64_t at, int j, const float *bias, float beta,
+                                           float *C, float *Z, const float *Zg)
+{
+    r += bias ? bias[j] : 0.f;
+    if (beta != 0.f) r += beta * C[at];
+    if (Z) {
+        Z[at] = r;
+        r = silu(r);
+    }
+    if (Zg) r *= silu_grad(Zg[at]);
+    C[at] = r;
+}
+
 // One 16 x 16 tile of C per workgroup on v_mfma_f32_16x16x4f32 (FP32 products and
 // sums), K split over the four wavefronts in runs of 16 and their sums added in
-// LDS.  The products of the training step are small (1,024 x 256 x 256 and
+// LDS.  The products of a training step are small (1,024 x 256 x 256 and
 // 256 x 256 x 1,024): what bounds them is the number of workgroups and the chain
-// along K, not the operand traffic, which L2 serves.  64 x 64 tiles with K in one
-// piece put 16 to 64 workgroups on 256 compute units: 99 us a product on average,
-// 14 here.
+// along K, not the operand traffic, which L2 serves.  The 64 x 64 tiles below put
+// 16 to 64 workgroups on 256 compute units there: 99 us a product on average, 14
+// here.
 __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float *A, int64_t sa0,
                                               int64_t sa1, const int32_t *gather, const float *B,
                                               int64_t sb0, int64_t sb1, const float *bias,
@@ -190,17 +202,61 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float *
     __syncthreads();
     const int u = threadIdx.x >> 4, v = threadIdx.x & 15;
     const int i = i0 + u, j = j0 + v;
-    if (i < M && j < N) {
-        float r = ((part[0][u][v] + part[1][u][v]) + part[2][u][v]) + part[3][u][v];
-        r += bias ? bias[j] : 0.f;
-        if (beta != 0.f) r += beta * C[i * ldc + j];
-        if (Z) {
-            Z[i * ldc + j] = r;
-            r = silu(r);
+    if (i < M && j < N)
+        gemm_store(((part[0][u][v] + part[1][u][v]) + part[2][u][v]) + part[3][u][v], i * ldc + j, j, bias,
+                   beta, C, Z, Zg);
+}
+
+// The same by 64 x 64 tiles staged in LDS, 4 x 4 values per thread: each operand is
+// read once per 64 rows instead of once per 16.  For products of so many tiles that
+// the operand traffic bounds them (the rule is launch_gemm's).
+constexpr int TB = 64, TK = 16;
+__global__ void __launch_bounds__(256) k_gemm_tile(int M, int N, int K, const float *A, int64_t sa0,
+                                                   int64_t sa1, const int32_t *gather, const float *B,
+                                                   int64_t sb0, int64_t sb1, const float *bias,
+                                                   float beta, float *C, int64_t ldc, float *Z,
+                                                   const float *Zg)
+{
+    __shared__ float sA[TK][TB + 1], sB[TK][TB + 1];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int i0 = blockIdx.y * TB, j0 = blockIdx.x * TB;
+    float acc[4][4] = {};
+    for (int k0 = 0; k0 < K; k0 += TK) {
+        for (int e = threadIdx.x; e < TK * TB; e += 256) {
+            const int kk = e / TB, ii = e - kk * TB;
+            const int i = i0 + ii, k = k0 + kk;
+            float v = 0.f;
+            if (i < M && k < K) {
+                const int64_t ri = gather ? gather[i] : i;
+                v = A[ri * sa0 + k * sa1];
+            }
+            sA[kk][ii] = v;
+            const int j = j0 + ii;
+            sB[kk][ii] = (j < N && k < K) ? B[k * sb0 + j * sb1] : 0.f;
         }
-        if (Zg) r *= silu_grad(Zg[i * ldc + j]);
-        C[i * ldc + j] = r;
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < TK; ++kk) {
+            float a[4], b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = sA[kk][ty * 4 + u];
+                b[u] = sB[kk][tx * 4 + u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * b[v];
+        }
+        __syncthreads();
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + ty * 4 + u, j = j0 + tx * 4 + v;
+            if (i < M && j < N) gemm_store(acc[u][v], i * ldc + j, j, bias, beta, C, Z, Zg);
+        }
 }
 
 // dY = 2 (Y - T) / (n * no); partial sums of (Y - T)^2 per block.
@@ -336,13 +392,20 @@ hipError_t launch_gemm(int M, int N, int K, const float *A, int64_t sa0, int64_t
                        const float *bias, float beta, float *C, int64_t ldc, float *Z,
                        const float *Zg, hipStream_t st)
 {
+    // The 64 x 64 tiles once there are 640 of them (2.5 per compute unit).  Forward
+    // pass in FP32 (196 -> 256 -> 256 -> 48) of 10,240, 16,384, 65,536 and 300,000
+    // rows: 177, 208, 526 and 2,109 us; 16 x 16 tiles throughout 177, 253, 929 and
+    // 4,149, 64 x 64 throughout 214, 234, 524 and 2,105.
+    const bool large = (int64_t)((M + TB - 1) / TB) * ((N + TB - 1) / TB) >= 640;
+    const int tile = large ? TB : 16;
     // at most 65,535 row tiles per launch
-    for (int i0 = 0; i0 < M; i0 += 16 * 65535) {
-        const int rows = std::min(M - i0, 16 * 65535);
-        dim3 grid((N + 15) / 16, (rows + 15) / 16);
-        hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, rows, N, K, gather ? A : A + i0 * sa0, sa0,
-                           sa1, gather ? gather + i0 : nullptr, B, sb0, sb1, bias, beta, C + i0 * ldc,
-                           ldc, Z ? Z + i0 * ldc : nullptr, Zg ? Zg + i0 * ldc : nullptr);
+    for (int64_t i0 = 0; i0 < M; i0 += 16 * 65535) {
+        const int rows = (int)std::min<int64_t>(M - i0, 16 * 65535);
+        dim3 grid((N + tile - 1) / tile, (rows + tile - 1) / tile);
+        hipLaunchKernelGGL(large ? k_gemm_tile : k_gemm, grid, dim3(256), 0, st, rows, N, K,
+                           gather ? A : A + i0 * sa0, sa0, sa1, gather ? gather + i0 : nullptr, B, sb0,
+                           sb1, bias, beta, C + i0 * ldc, ldc, Z ? Z + i0 * ldc : nullptr,
+                           Zg ? Zg + i0 * ldc : nullptr);
     }
     return hipGetLastError();
 }
