@@ -133,7 +133,8 @@ typedef struct {
     int32_t basis_kernel;   /* MA_BASIS_AUTO: the autotuned kernel for (p, q, precision)
                                if ma_autotune ran, else MA_BASIS_ONCHIP in its register
                                form (MA_PREC_FP64, o = 4, regions of at most 512
-                               orbitals, p + q <= 32); MA_BASIS_ATOM (MA_PREC_FP64,
+                               orbitals and 8 operator blocks per row, p + q <= 32);
+                               MA_BASIS_ATOM (MA_PREC_FP64,
                                o = 9, at least as many atoms as compute units and on
                                average 7 columns of each, and its workspaces fit);
                                else MA_BASIS_WORKSPACE.

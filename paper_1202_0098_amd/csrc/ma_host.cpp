@@ -1067,9 +1067,20 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     // kernel's resident form where it holds the shape (4,000 columns of 480
     // orbitals, nu = 30: basis 3.1 ms against 4.5), else the workspace kernel.
     // On-chip means the resident form wherever that holds the shape.
+    //
+    // Both up to a number of operator blocks per row of the largest region: the
+    // resident form holds two of a row's blocks and loads the others again for every
+    // product, from memory where the columns in flight lie far apart.  Against the
+    // workspace kernel, 480 orbitals, p = q = 8 and 4,000 columns in random order: 4.2
+    // blocks per row 1.21 times as fast, 8.8 0.99, 12 0.95 and 0.86 with p + q = 6
+    // (whole cells in order: 1.15 at 12, 0.71 at 40).  Against the LDS form, 2,000
+    // columns, p + q = 6: 1.5 times at 12, 0.99 at 19, 0.83 at 28.
+    constexpr int kAutoRowBlocks = 8, kOnchipRowBlocks = 18;
+    auto rows_at_most = [&](int64_t blocks) { return ctx->max_lnnz <= blocks * ctx->max_nat; };
     int want_kernel = opts.basis_kernel;
     if (want_kernel == MA_BASIS_AUTO && tn) want_kernel = tn->kernel;
-    const bool resident = (want_kernel == MA_BASIS_AUTO || (want_kernel == MA_BASIS_ONCHIP && fits)) &&
+    const bool resident = ((want_kernel == MA_BASIS_AUTO && rows_at_most(kAutoRowBlocks)) ||
+                           (want_kernel == MA_BASIS_ONCHIP && fits && rows_at_most(kOnchipRowBlocks))) &&
                           ma::basis_resident_fits(ctx->nmax, P.nu, q, ctx->o, opts.precision,
                                                   ma::lidx_bytes(ctx->max_nat, (int)ctx->max_lnnz));
     // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of 630

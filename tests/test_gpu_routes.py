@@ -1,0 +1,66 @@
+"""Which basis kernel a solve takes.  The caller workspace that a solve needs tells
+them apart: the on-chip kernel has no basis workspace, the workspace kernel one
+column's per workgroup, the atom kernel a whole atom's."""
+
+import numpy as np
+import pytest
+
+from paper_1202_0098_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    yield torch, ma
+
+
+def _sp3(cells, region, rcut=None):
+    prm = synth.SP3_PARAMS if rcut is None else dict(synth.SP3_PARAMS, rcut=rcut)
+    pos = synth.diamond_positions(*cells, 5.43)
+    pos = pos + np.random.default_rng(2).normal(0, 0.05, size=pos.shape)
+    s = synth.build_tb(pos, np.array(cells) * 5.43, prm, name="sp3")
+    s.region_mode, s.kT = "nearest", 0.1
+    s.region_nrp = np.full(s.n_atoms, region, np.int32)
+    return s
+
+
+def _size(ma, ctx, cols, p, q, kernel):
+    return ctx.workspace_size(cols, p, q, mu=0.9, opts=ma.default_opts(basis_kernel=kernel, pipeline=0))
+
+
+def _solve(torch, ma, ctx, s, p, q, kernel, cols=None):
+    rho = torch.zeros(s.nblk * 16, dtype=torch.float64, device="cuda")
+    ctx.solve_columns(cols, p, q, mu=0.9, kT=s.kT, rho=rho, opts=ma.default_opts(basis_kernel=kernel))
+    torch.cuda.synchronize()
+    return rho.cpu().numpy()
+
+
+# (cutoff: operator blocks per row of the largest region)
+@pytest.mark.parametrize("rcut,rows,onchip", [(None, (3, 8), True), (4.2, (8, 18), False),
+                                              (5.6, (18, 40), False)])
+def test_dense_operators_leave_the_register_form(env, rcut, rows, onchip):
+    """Up to 8 blocks per row the automatic kernel is the on-chip one, past that the
+    workspace kernel; the named on-chip kernel goes back to its LDS form past 18."""
+    torch, ma = env
+    import oracle
+    s = _sp3((4, 4, 4), 100, rcut)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    na, lb = ctx.region_sizes(s.n_atoms)
+    assert rows[0] < lb.max() / na.max() <= rows[1]
+    cols = np.sort(np.random.default_rng(3).choice(s.n_atoms, 6, replace=False))
+    cols = (4 * cols[:, None] + np.arange(4)).ravel().astype(np.int32)
+    auto, on, work = (_size(ma, ctx, cols, 6, 5, k) for k in ("auto", "onchip", "workspace"))
+    assert on < work and auto == (on if onchip else work)
+    raw = oracle.solve_raw(s, cols=cols, p=6, q=5)
+    want = oracle.scatter_slots(s, cols, oracle.outputs(s, raw, 0.9, s.kT)[0])
+    for kernel in ("auto", "onchip"):
+        print(f"[gpu-case] cutoff {rcut} {kernel}", flush=True)
+        got = _solve(torch, ma, ctx, s, 6, 5, kernel, cols).reshape(-1, 4, 4)
+        assert np.abs(got - want).max() <= 1e-10     # the parity tests' FP64 bound
+    ctx.close()
