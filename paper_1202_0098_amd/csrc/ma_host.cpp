@@ -1826,10 +1826,14 @@ MA_API ma_status ma_forces(ma_ctx *ctx, const double *dH, const double *dS, cons
     HIPCHK(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     hipStream_t st = ctx->work_stream();
     HIPCHK(ctx, ctx->after_caller(), "stream order");
-    HIPCHK(ctx, ctx->force_g.reserve(sizeof(double) * 3 * (size_t)ctx->nblk), "forces");
+    double *g = nullptr;
+    if (ma::forces_need_blocks(ctx->o, ctx->nblk)) {
+        HIPCHK(ctx, ctx->force_g.reserve(sizeof(double) * 6 * (size_t)ctx->nblk), "forces");
+        g = ctx->force_g.as<double>();
+    }
     HIPCHK(ctx, ma::launch_forces(ctx->n_atoms, ctx->o, ctx->blk_ptr.as<int64_t>(),
                                   ctx->blk_col.as<int32_t>(), ctx->blk_t.as<int32_t>(), dH, dS, rho,
-                                  pi, spin, ctx->nblk, ctx->force_g.as<double>(), forces, st), "forces");
+                                  pi, spin, ctx->nblk, g, forces, st), "forces");
     HIPCHK(ctx, hipStreamSynchronize(st), "forces");
     return MA_OK;
 }

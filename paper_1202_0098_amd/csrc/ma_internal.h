@@ -160,6 +160,9 @@ hipError_t launch_sum2(const double *a, const double *b, int n, double *out, hip
 
 // Forces, density of states and Green's function from a solve's outputs
 // (ma_post.hip).
+// (g: 6 doubles per block where forces_need_blocks says so; null: in one launch,
+// without them)
+bool forces_need_blocks(int o, int64_t nblk);
 hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32_t *blk_col,
                          const int32_t *blk_t, const double *dH, const double *dS,
                          const double *rho, const double *pi, double spin, int64_t nblk,

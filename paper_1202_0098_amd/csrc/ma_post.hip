@@ -24,10 +24,136 @@ namespace {
 // rows i = (B, c); dH_k is the derivative of H_AB with respect to R_B, so
 // g_k enters F_A with + and F_B with -.
 //
-// First g_k: LPB lanes per block, which reads every value once.  Bound by
-// those bytes (64 o^2 per block): 2,048 spd atoms 86 us and 4 us for the sum below;
-// one wavefront per atom over its blocks and their transposes, which read every
-// block twice, took 122 us.
+// The g of an atom nearly cancel, so that their own rounding would be most of the
+// result's error: sums carry what their additions round off (Knuth's two-sum) to
+// the end.  Not a number there where the sum itself is not finite; such a sum is
+// taken as it is.
+struct Sum2 {
+    double h = 0.0, l = 0.0;
+    __device__ __forceinline__ void add(double v)
+    {
+        const double s = h + v, w = s - h;
+        l += (h - (s - w)) + (v - w);
+        h = s;
+    }
+    __device__ __forceinline__ void add(const Sum2 &v)
+    {
+        add(v.h);
+        l += v.l;
+    }
+    __device__ __forceinline__ double value() const { return isfinite(h) ? h + l : h; }
+};
+
+template <int CTRL>
+__device__ __forceinline__ void add_dpp(Sum2 &s, const Sum2 &from)
+{
+    Sum2 o;
+    o.h = dpp<CTRL>(from.h);
+    o.l = dpp<CTRL>(from.l);
+    s.add(o);
+}
+
+// Exchange steps of a transposed reduction: a's sum in one half of the lanes,
+// b's in the other (where `other` holds).
+__device__ __forceinline__ void fold32(Sum2 &a, Sum2 b)
+{
+    swap32(a.h, b.h);
+    swap32(a.l, b.l);
+    a.add(b);
+}
+
+__device__ __forceinline__ void fold16(Sum2 &a, Sum2 b)
+{
+    swap16(a.h, b.h);
+    swap16(a.l, b.l);
+    a.add(b);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void fold_dpp(Sum2 &a, const Sum2 &b, bool other)
+{
+    Sum2 send;
+    send.h = other ? a.h : b.h;
+    send.l = other ? a.l : b.l;
+    a.h = other ? b.h : a.h;
+    a.l = other ? b.l : a.l;
+    add_dpp<CTRL>(a, send);
+}
+
+// Sums over each group of W lanes (4, 16 or 64) of three values per lane; value v's
+// ends in s[0] of the group's lane first_lane<W>(v).
+template <int W>
+__device__ __forceinline__ int first_lane(int v)
+{
+    return v == 0 ? 0 : W == 64 ? (v == 1 ? 16 : 32) : W == 16 ? (v == 1 ? 8 : 4) : (v == 1 ? 2 : 1);
+}
+
+template <int W>
+__device__ __forceinline__ void group_sums(Sum2 (&s)[3])
+{
+    const int l = threadIdx.x;
+    if constexpr (W == 64) {
+        fold32(s[0], s[2]);
+        fold32(s[1], Sum2());
+        fold16(s[0], s[1]);
+        add_dpp<kDppRor8>(s[0], s[0]);
+        add_dpp<kDppHalfMirror>(s[0], s[0]);
+        add_dpp<kDppXor2>(s[0], s[0]);
+        add_dpp<kDppXor1>(s[0], s[0]);
+    } else if constexpr (W == 16) {
+        fold_dpp<kDppRor8>(s[0], s[1], (l & 8) != 0);
+        add_dpp<kDppRor8>(s[2], s[2]);
+        fold_dpp<kDppHalfMirror>(s[0], s[2], (l & 4) != 0);
+        add_dpp<kDppXor2>(s[0], s[0]);
+        add_dpp<kDppXor1>(s[0], s[0]);
+    } else {
+        fold_dpp<kDppXor2>(s[0], s[1], (l & 2) != 0);
+        add_dpp<kDppXor2>(s[2], s[2]);
+        fold_dpp<kDppXor1>(s[0], s[2], (l & 1) != 0);
+    }
+}
+
+// Small patterns, in one launch: one wavefront per atom, LPB lanes per block.  It
+// reads every block twice (as k and as T(k)), which costs less than a second
+// launch while the blocks are few and small.
+template <int LPB>
+__global__ void __launch_bounds__(64) k_forces_direct(int n_atoms, int oo, const int64_t *blk_ptr,
+                                                      const int32_t *blk_col, const int32_t *blk_t,
+                                                      const double *dH, const double *dS,
+                                                      const double *rho, const double *pi,
+                                                      double spin, double *F)
+{
+    const int lane = threadIdx.x;
+    for (int X = blockIdx.x; X < n_atoms; X += gridDim.x) {
+        Sum2 f[3];
+        for (int64_t k = blk_ptr[X] + lane / LPB; k < blk_ptr[X + 1]; k += 64 / LPB) {
+            if (blk_col[k] == X) continue;
+            const int64_t kt = blk_t[k];
+            for (int e = lane % LPB; e < oo; e += LPB) {
+                const double ra = rho[k * oo + e], pa = pi[k * oo + e];
+                const double rb = rho[kt * oo + e], pb = pi[kt * oo + e];
+                const double *ha = dH + k * 3 * oo + e, *sa = dS + k * 3 * oo + e;
+                const double *hb = dH + kt * 3 * oo + e, *sb = dS + kt * 3 * oo + e;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    f[d].add(ra * ha[d * oo] - pa * sa[d * oo]);
+                    f[d].add(pb * sb[d * oo] - rb * hb[d * oo]);
+                }
+            }
+        }
+        group_sums<64>(f);
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            if (lane == first_lane<64>(d)) F[3 * (int64_t)X + d] = spin * f[0].value();
+    }
+}
+
+// Otherwise g_k first, which reads every value once: sums and carries, six doubles
+// per block, LPB lanes per block (a quarter of the lanes, with fewer lines of memory
+// in flight: 1.4 times the time).  Bound by the bytes (64 o^2 per block): 2,048 spd
+// atoms 67 us and 4 us for the sums below, where one wavefront per atom with the
+// blocks and their transposes took 122; error in the 2-norm 4.9e-17 of the
+// forces, with plain sums 2.3e-16, by one wavefront per atom 1.2e-16.
 template <int LPB>
 __global__ void __launch_bounds__(256) k_block_forces(int64_t nblk, int oo, const double *dH,
                                                       const double *dS, const double *rho,
@@ -37,42 +163,58 @@ __global__ void __launch_bounds__(256) k_block_forces(int64_t nblk, int oo, cons
     const int l = threadIdx.x % LPB;
     for (int64_t k = (int64_t)blockIdx.x * BPW + threadIdx.x / LPB; k - threadIdx.x / LPB < nblk;
          k += (int64_t)gridDim.x * BPW) {
-        double f0 = 0.0, f1 = 0.0, f2 = 0.0;
-        if (k < nblk)
+        Sum2 f[3];
+        if (k < nblk && l < oo) {
+            // (the first terms need no additions)
+            auto term = [&](int e, int d) __attribute__((always_inline)) {
+                const int64_t at = (k * 3 + d) * oo + e;
+                return rho[k * oo + e] * dH[at] - pi[k * oo + e] * dS[at];
+            };
+#pragma unroll
+            for (int d = 0; d < 3; ++d) f[d].h = term(l, d);
 #pragma unroll 2
-            for (int e = l; e < oo; e += LPB) {
-                const double r = rho[k * oo + e], p = pi[k * oo + e];
-                const double *h = dH + k * 3 * oo + e, *s = dS + k * 3 * oo + e;
-                f0 += r * h[0] - p * s[0];
-                f1 += r * h[oo] - p * s[oo];
-                f2 += r * h[2 * oo] - p * s[2 * oo];
-            }
-        f0 = sum_within<LPB>(f0);
-        f1 = sum_within<LPB>(f1);
-        f2 = sum_within<LPB>(f2);
-        if (l < 3 && k < nblk) g[3 * k + l] = l == 0 ? f0 : l == 1 ? f1 : f2;
+            for (int e = l + LPB; e < oo; e += LPB)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) f[d].add(term(e, d));
+        }
+        group_sums<LPB>(f);
+        if (k < nblk)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if (l == first_lane<LPB>(d)) {
+                    g[6 * k + d] = f[0].h;
+                    g[6 * k + 3 + d] = f[0].l;
+                }
     }
 }
 
-// Then the sum over an atom's blocks, one wavefront per atom.
+// Then the sum over an atom's blocks, LPA lanes per atom.
+template <int LPA>
 __global__ void __launch_bounds__(256) k_forces(int n_atoms, const int64_t *blk_ptr,
                                                 const int32_t *blk_col, const int32_t *blk_t,
                                                 const double *g, double spin, double *F)
 {
-    const int lane = threadIdx.x & 63;
-    for (int X = blockIdx.x * 4 + (threadIdx.x >> 6); X < n_atoms; X += gridDim.x * 4) {
-        double f0 = 0.0, f1 = 0.0, f2 = 0.0;
-        for (int64_t k = blk_ptr[X] + lane; k < blk_ptr[X + 1]; k += 64) {
-            if (blk_col[k] == X) continue;
-            const double *a = g + 3 * k, *b = g + 3 * (int64_t)blk_t[k];
-            f0 += a[0] - b[0];
-            f1 += a[1] - b[1];
-            f2 += a[2] - b[2];
-        }
-        f0 = sum_within<64>(f0);
-        f1 = sum_within<64>(f1);
-        f2 = sum_within<64>(f2);
-        if (lane < 3) F[3 * (int64_t)X + lane] = spin * (lane == 0 ? f0 : lane == 1 ? f1 : f2);
+    constexpr int APW = 256 / LPA;   // atoms per workgroup
+    const int l = threadIdx.x % LPA, sub = threadIdx.x / LPA;
+    for (int X0 = blockIdx.x * APW; X0 < n_atoms; X0 += gridDim.x * APW) {
+        const int X = X0 + sub;
+        Sum2 f[3];
+        if (X < n_atoms)
+            for (int64_t k = blk_ptr[X] + l; k < blk_ptr[X + 1]; k += LPA) {
+                if (blk_col[k] == X) continue;
+                const double *a = g + 6 * k, *b = g + 6 * (int64_t)blk_t[k];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    f[d].add(a[d]);
+                    f[d].add(-b[d]);
+                    f[d].l += a[3 + d] - b[3 + d];
+                }
+            }
+        group_sums<LPA>(f);
+        if (X < n_atoms)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if (l == first_lane<LPA>(d)) F[3 * (int64_t)X + d] = spin * f[0].value();
     }
 }
 
@@ -249,6 +391,11 @@ hipError_t launch_map_sj(int ncols, const int32_t *cols, int o, RegionView cur, 
     return hipGetLastError();
 }
 
+// Up to 16 values per block (o <= 4) and 24,576 blocks one launch: 4,096 sp3 atoms
+// (20,480 blocks) 38.2 us with the call's synchronisation, in two launches 41.5;
+// 5,832 atoms in two 40.0, by one wavefront per atom 45.8.
+bool forces_need_blocks(int o, int64_t nblk) { return o > 4 || nblk > 24576; }
+
 hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32_t *blk_col,
                          const int32_t *blk_t, const double *dH, const double *dS,
                          const double *rho, const double *pi, double spin, int64_t nblk,
@@ -256,14 +403,22 @@ hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32
 {
     const int oo = o * o;
     auto grid = [](int64_t n) { return dim3((unsigned)(n < (1 << 20) ? n : (1 << 20))); };
+    if (!g) {
+        hipLaunchKernelGGL(k_forces_direct<16>, grid(n_atoms), dim3(64), 0, st, n_atoms, oo, blk_ptr, blk_col, blk_t, dH, dS, rho, pi, spin, F);
+        return hipGetLastError();
+    }
     if (oo <= 16)
         hipLaunchKernelGGL(k_block_forces<16>, grid((nblk + 15) / 16), dim3(256), 0, st, nblk, oo, dH, dS,
                            rho, pi, g);
     else
         hipLaunchKernelGGL(k_block_forces<64>, grid((nblk + 3) / 4), dim3(256), 0, st, nblk, oo, dH, dS,
                            rho, pi, g);
-    hipLaunchKernelGGL(k_forces, grid((n_atoms + 3) / 4), dim3(256), 0, st, n_atoms, blk_ptr, blk_col,
-                       blk_t, g, spin, F);
+    if (nblk <= 16 * (int64_t)n_atoms)
+        hipLaunchKernelGGL(k_forces<16>, grid((n_atoms + 15) / 16), dim3(256), 0, st, n_atoms, blk_ptr,
+                           blk_col, blk_t, g, spin, F);
+    else
+        hipLaunchKernelGGL(k_forces<64>, grid((n_atoms + 3) / 4), dim3(256), 0, st, n_atoms, blk_ptr,
+                           blk_col, blk_t, g, spin, F);
     return hipGetLastError();
 }
 
