@@ -1103,8 +1103,8 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         auto_atom = atoms >= ctx->cu_count && ncols >= 7 * atoms;
     }
     if (want_kernel == MA_BASIS_AUTO) want_kernel = auto_atom ? MA_BASIS_ATOM : MA_BASIS_WORKSPACE;
-    // (its workgroups' workspaces are larger: where they do not fit, the plan
-    // is made again with the workspace kernel)
+    // (its workgroups' workspaces are larger: where they, or what the solve needs
+    // beside them, do not fit, the plan is made again with the workspace kernel)
     auto without_atom = [&] {
         (void)hipGetLastError();
         src->off = src_off;
@@ -1375,25 +1375,38 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
             return ctx->fail(MA_EINVAL, "the solve needs %zu bytes of workspace, %zu given",
                              src->off, src->cap);
     } else {
-        HIPCHK(ctx, ctx->lists.reserve(n_lists), "column lists");
         if (auto_atom && slot_bytes * P.slots > ctx->ws.bytes) {
             size_t fr = 0, tot = 0;
             if (hipMemGetInfo(&fr, &tot) != hipSuccess || slot_bytes * P.slots > (fr + ctx->ws.bytes) / 2)
                 return without_atom();
         }
-        if (slot_bytes) HIPCHK(ctx, ctx->ws.reserve(slot_bytes * P.slots), "workspace");
-        HIPCHK(ctx, ctx->mid.reserve(n_mid), "chunk buffer");
-        if (n_eps) HIPCHK(ctx, ctx->eps.reserve(n_eps), "eps");
-        if (n_wts) HIPCHK(ctx, ctx->wts.reserve(n_wts), "wts");
-        if (n_amp) HIPCHK(ctx, ctx->amp.reserve(n_amp), "amplitudes");
-        if (n_stats) HIPCHK(ctx, ctx->stats.reserve(n_stats), "stats");
-        if (n_feat) HIPCHK(ctx, ctx->feat.reserve(n_feat), "descriptors");
-        if (n_x0) HIPCHK(ctx, ctx->x0.reserve(n_x0), "start vectors");
-        if (n_x0full) HIPCHK(ctx, ctx->x0full.reserve(n_x0full), "previous start vectors");
-        HIPCHK(ctx, ctx->ctl.reserve(n_ctl), "ctl");
-        HIPCHK(ctx, ctx->partial.reserve(n_partial), "partial");
-        HIPCHK(ctx, ctx->Ecol.reserve(n_E), "Ecol");
-        HIPCHK(ctx, ctx->Ncol.reserve(n_E), "Ncol");
+        hipError_t grown = hipSuccess;
+        const char *what = "";
+        auto grow = [&](DevBuf &buf, size_t n, const char *name) {
+            if (grown != hipSuccess || n == 0) return;
+            grown = buf.reserve(n);
+            what = name;
+        };
+        grow(ctx->lists, n_lists, "column lists");
+        grow(ctx->ws, slot_bytes * P.slots, "workspace");
+        grow(ctx->mid, n_mid, "chunk buffer");
+        grow(ctx->eps, n_eps, "eps");
+        grow(ctx->wts, n_wts, "wts");
+        grow(ctx->amp, n_amp, "amplitudes");
+        grow(ctx->stats, n_stats, "stats");
+        grow(ctx->feat, n_feat, "descriptors");
+        grow(ctx->x0, n_x0, "start vectors");
+        grow(ctx->x0full, n_x0full, "previous start vectors");
+        grow(ctx->ctl, n_ctl, "ctl");
+        grow(ctx->partial, n_partial, "partial");
+        grow(ctx->Ecol, n_E, "Ecol");
+        grow(ctx->Ncol, n_E, "Ncol");
+        if (grown != hipSuccess && auto_atom) {
+            ctx->ws.release();
+            ctx->mid.release();
+            return without_atom();
+        }
+        HIPCHK(ctx, grown, what);
         b_lists = ctx->lists.p;
         b_ws = slot_bytes ? ctx->ws.p : nullptr;
         b_mid = ctx->mid.p;

@@ -1,0 +1,69 @@
+"""Solves on a card whose memory is mostly held by the caller: the automatic kernel
+falls back to the one that fits."""
+
+import numpy as np
+import pytest
+
+from paper_1202_0098_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1202_0098_amd as ma
+    yield torch, ma
+
+
+def _hold(torch, leave):
+    """Device memory of the caller's, so that `leave` bytes are free (what the runtime
+    says is free grows by some of its own when a large piece is taken: twice)."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(3):
+        more = (torch.cuda.mem_get_info()[0] - leave) // (2 * MB) * (2 * MB)
+        if more > 0:
+            held.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
+    assert abs(torch.cuda.mem_get_info()[0] - leave) <= 8 * MB
+    return held
+
+
+def test_automatic_kernel_where_its_other_buffers_do_not_fit(env):
+    """The atom kernel's workspaces fit half of the free memory, but not all of the
+    solve's buffers beside them; the workspace kernel's do."""
+    torch, ma = env
+    s = synth.config_fcc_spd(5, cells=(8, 8, 12))
+    p, q, n = 4, 3, s.nblk * 81
+    opts = {k: ma.default_opts(basis_kernel=k, pipeline=0, slots_per_cu=1) for k in ("auto", "atom", "workspace")}
+    rho = torch.zeros(n, dtype=torch.float64, device="cuda")
+    ref = torch.zeros_like(rho)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["atom"])   # (kernels loaded)
+    want = ctx.solve_columns(None, p, q, kT=s.kT, rho=ref, opts=opts["workspace"])
+    ctx.close()
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    auto, atom, work = (ctx.workspace_size(None, p, q, opts=opts[k]) for k in ("auto", "atom", "workspace"))
+    leave = atom - 200 * MB
+    assert auto == atom and work + 100 * MB <= leave
+    held = _hold(torch, leave)
+    try:
+        print(f"[gpu-case] {leave / MB:.0f} MB free, atom {atom / MB:.0f}, workspace {work / MB:.0f}",
+              flush=True)
+        rho.zero_()
+        got = ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["auto"])
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert torch.equal(rho, ref) and got.mu == want.mu and got.energy == want.energy
+    # with the memory back, the atom kernel again
+    got = ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["auto"])
+    assert float((rho - ref).abs().max()) <= 1e-10     # the parity tests' bound between kernels
+    ctx.close()
