@@ -1839,10 +1839,13 @@ MA_API ma_status ma_forces(ma_ctx *ctx, const double *dH, const double *dS, cons
     HIPCHK(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     hipStream_t st = ctx->work_stream();
     HIPCHK(ctx, ctx->after_caller(), "stream order");
+    // (where the block sums do not fit, in one launch without them)
     double *g = nullptr;
     if (ma::forces_need_blocks(ctx->o, ctx->nblk)) {
-        HIPCHK(ctx, ctx->force_g.reserve(sizeof(double) * 6 * (size_t)ctx->nblk), "forces");
-        g = ctx->force_g.as<double>();
+        if (ctx->force_g.reserve(sizeof(double) * 6 * (size_t)ctx->nblk) == hipSuccess)
+            g = ctx->force_g.as<double>();
+        else
+            (void)hipGetLastError();
     }
     HIPCHK(ctx, ma::launch_forces(ctx->n_atoms, ctx->o, ctx->blk_ptr.as<int64_t>(),
                                   ctx->blk_col.as<int32_t>(), ctx->blk_t.as<int32_t>(), dH, dS, rho,

@@ -113,9 +113,9 @@ __device__ __forceinline__ void group_sums(Sum2 (&s)[3])
     }
 }
 
-// Small patterns, in one launch: one wavefront per atom, LPB lanes per block.  It
-// reads every block twice (as k and as T(k)), which costs less than a second
-// launch while the blocks are few and small.
+// In one launch: one wavefront per atom, LPB lanes per block.  It reads every block
+// twice (as k and as T(k)), which costs less than a second launch while the blocks
+// are few and small; also where there is no memory for the block sums.
 template <int LPB>
 __global__ void __launch_bounds__(64) k_forces_direct(int n_atoms, int oo, const int64_t *blk_ptr,
                                                       const int32_t *blk_col, const int32_t *blk_t,
@@ -404,7 +404,8 @@ hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32
     const int oo = o * o;
     auto grid = [](int64_t n) { return dim3((unsigned)(n < (1 << 20) ? n : (1 << 20))); };
     if (!g) {
-        hipLaunchKernelGGL(k_forces_direct<16>, grid(n_atoms), dim3(64), 0, st, n_atoms, oo, blk_ptr, blk_col, blk_t, dH, dS, rho, pi, spin, F);
+        hipLaunchKernelGGL(oo <= 16 ? k_forces_direct<16> : k_forces_direct<64>, grid(n_atoms), dim3(64), 0,
+                           st, n_atoms, oo, blk_ptr, blk_col, blk_t, dH, dS, rho, pi, spin, F);
         return hipGetLastError();
     }
     if (oo <= 16)

@@ -1,5 +1,5 @@
-"""Solves on a card whose memory is mostly held by the caller: the automatic kernel
-falls back to the one that fits."""
+"""Calls on a card whose memory is mostly held by the caller: the automatic kernel
+falls back to the one that fits, the forces to one launch without block sums."""
 
 import numpy as np
 import pytest
@@ -67,3 +67,36 @@ def test_automatic_kernel_where_its_other_buffers_do_not_fit(env):
     got = ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["auto"])
     assert float((rho - ref).abs().max()) <= 1e-10     # the parity tests' bound between kernels
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["sp3", "spd"])
+def test_forces_without_memory_for_the_block_sums(env, kind):
+    """One launch instead of two; both carry the rounding of their sums, so that they
+    agree to the rounding of the result (2^-53 of the largest, twice)."""
+    torch, ma = env
+    if kind == "sp3":
+        s = synth.build_tb(synth.diamond_positions(22, 22, 22, 5.43), np.full(3, 5.43 * 22), synth.SP3_PARAMS)
+        s.region_mode, s.region_nrp = "nearest", np.full(s.n_atoms, 5, np.int32)
+    else:
+        s = synth.config_fcc_spd(5, cells=(12, 12, 12))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rho, pi = (torch.randn(s.nblk * s.n_orb ** 2, dtype=torch.float64, device="cuda", generator=g)
+               for _ in range(2))
+    dH, dS = (torch.randn(3 * s.nblk * s.n_orb ** 2, dtype=torch.float64, device="cuda", generator=g)
+              for _ in range(2))
+    F, ref = (torch.zeros(3 * s.n_atoms, dtype=torch.float64, device="cuda") for _ in range(2))
+    for out in (ref, F):
+        ctx = ma.Context(0)
+        ctx.build_tb(s)
+        held = []
+        if out is F:   # the sums take 48 bytes per block
+            held = _hold(torch, 4 * MB)
+            assert 48 * s.nblk > torch.cuda.mem_get_info()[0]
+        print(f"[gpu-case] forces, {s.nblk} blocks, {torch.cuda.mem_get_info()[0] / MB:.0f} MB free", flush=True)
+        try:
+            ctx.forces(dH, dS, rho, pi, out)
+        finally:
+            del held
+            torch.cuda.empty_cache()
+        ctx.close()
+    assert float((F - ref).abs().max()) <= 2 ** -52 * float(ref.abs().max())
