@@ -1870,10 +1870,20 @@ MA_API ma_status ma_dos(ma_ctx *ctx, int64_t n_energies, const double *energies,
     HIPCHK(ctx, ctx->after_caller(), "stream order");
     HIPCHK(ctx, ctx->dos_E.reserve(sizeof(double) * nE), "energies");
     HIPCHK(ctx, ctx->dos_out.reserve(sizeof(double) * nE), "dos");
-    HIPCHK(ctx, ctx->dos_part.reserve(sizeof(double) * std::max<size_t>(1, ma::dos_partial_doubles(J.ncols, J.nu, nE))), "dos partials");
+    auto partials = [&](int64_t chunk) {
+        return ctx->dos_part.reserve(sizeof(double) *
+                                     std::max<size_t>(1, ma::dos_partial_doubles(J.ncols, J.nu, nE, chunk)));
+    };
+    int64_t chunk = ma::dos_chunk(J.ncols, J.nu, nE);
+    if (partials(chunk) != hipSuccess) {
+        // (fewer, longer chunks where the partial sums do not fit)
+        (void)hipGetLastError();
+        chunk = ma::kDosChunkMax;
+        HIPCHK(ctx, partials(chunk), "dos partials");
+    }
     HIPCHK(ctx, hipMemcpyAsync(ctx->dos_E.p, energies, sizeof(double) * nE, hipMemcpyHostToDevice, st), "energies");
     HIPCHK(ctx, ma::launch_dos(J.eps, J.wts, J.stats, J.ncols, J.nu, ctx->dos_E.as<double>(), nE, eta,
-                               spin, ctx->dos_part.as<double>(), ctx->dos_out.as<double>(), st), "dos");
+                               spin, chunk, ctx->dos_part.as<double>(), ctx->dos_out.as<double>(), st), "dos");
     HIPCHK(ctx, hipMemcpyAsync(dos, ctx->dos_out.p, sizeof(double) * nE, hipMemcpyDeviceToHost, st), "dos");
     HIPCHK(ctx, hipStreamSynchronize(st), "dos");
     return MA_OK;

@@ -167,10 +167,14 @@ hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32
                          const int32_t *blk_t, const double *dH, const double *dS,
                          const double *rho, const double *pi, double spin, int64_t nblk,
                          double *g, double *F, hipStream_t st);
-size_t dos_partial_doubles(int ncols, int nu, int nE);
+// (chunk: Ritz pairs per workgroup, dos_chunk's choice or kDosChunkMax, which takes
+// the least memory)
+constexpr int64_t kDosChunkMax = 8192;
+int64_t dos_chunk(int ncols, int nu, int nE);
+size_t dos_partial_doubles(int ncols, int nu, int nE, int64_t chunk);
 hipError_t launch_dos(const double *eps, const double *wts, const int32_t *stats, int ncols,
-                      int nu, const double *E, int nE, double eta, double spin, double *part,
-                      double *out, hipStream_t st);
+                      int nu, const double *E, int nE, double eta, double spin, int64_t chunk,
+                      double *part, double *out, hipStream_t st);
 hipError_t launch_green(const DevSystem &S, const DevJob &J, double zr, double zi, double *gre,
                         double *gim, hipStream_t st);
 // Map kept s_j (old regions) onto the current regions: x0full[c][i].

@@ -219,15 +219,21 @@ __global__ void __launch_bounds__(256) k_forces(int n_atoms, const int64_t *blk_
 }
 
 constexpr int kDosStage = 1024;   // Ritz pairs staged at a time by the DOS kernel
+static_assert(kDosChunkMax % kDosStage == 0, "whole stages");
 constexpr int kDosTile = 512;     // energies per workgroup, two per thread
+
+}  // namespace
 
 // Ritz pairs per workgroup: stages of 1,024 until the launch has 2,048
 // workgroups, at most eight (which bounds the partial sums)
-int64_t dos_chunk(int64_t npairs, int nE)
+int64_t dos_chunk(int ncols, int nu, int nE)
 {
+    const int64_t npairs = (int64_t)ncols * nu;
     const int64_t wgs = (npairs + kDosStage - 1) / kDosStage * ((nE + kDosTile - 1) / kDosTile);
-    return kDosStage * std::max<int64_t>(1, std::min<int64_t>(8, wgs / 2048));
+    return std::max<int64_t>(kDosStage, std::min<int64_t>(kDosChunkMax, wgs / 2048 * kDosStage));
 }
+
+namespace {
 
 // Partial DOS of one chunk of Ritz pairs (staged in LDS) at a tile of
 // energies: part[chunk][E] (thread t takes energies tile * 512 + t and + 256).
@@ -423,19 +429,17 @@ hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32
     return hipGetLastError();
 }
 
-size_t dos_partial_doubles(int ncols, int nu, int nE)
+size_t dos_partial_doubles(int ncols, int nu, int nE, int64_t chunk)
 {
     const int64_t npairs = (int64_t)ncols * nu;
-    const int64_t chunk = dos_chunk(npairs, nE);
     return (size_t)((npairs + chunk - 1) / chunk) * nE;
 }
 
 hipError_t launch_dos(const double *eps, const double *wts, const int32_t *stats, int ncols,
-                      int nu, const double *E, int nE, double eta, double spin, double *part,
-                      double *out, hipStream_t st)
+                      int nu, const double *E, int nE, double eta, double spin, int64_t chunk,
+                      double *part, double *out, hipStream_t st)
 {
     const int64_t npairs = (int64_t)ncols * nu;
-    const int64_t chunk = dos_chunk(npairs, nE);
     const int nchunks = (int)((npairs + chunk - 1) / chunk);
     const int tiles = (nE + kDosTile - 1) / kDosTile;
     if (nchunks < 1 || tiles < 1) return hipSuccess;
