@@ -154,7 +154,11 @@ typedef struct {
                                MA_PREC_MIXED_F64ACC).  A forced kernel that cannot
                                hold the shape is MA_EINVAL. */
     int32_t chunk_columns;  /* columns per chunk of the processing order (0 = as many
-                               as a 4 GiB chunk buffer holds); a solve of several
+                               as the chunk buffer holds: 4 GiB of each of a pipelined
+                               solve's and in a caller's workspace; 8 GiB where the
+                               chunks run in sequence by default, see pipeline; a fifth
+                               of the free device memory, between 4 and 64 GiB, where
+                               pipeline or a tuning says so); a solve of several
                                chunks launches eagerly instead of replaying graphs */
     int32_t pipeline;       /* >= 2: a solve of at least 2048 * pipeline columns is cut
                                into pipeline + 2 chunks of geometrically falling size

@@ -945,8 +945,9 @@ struct Plan {
 // one chunk (the rest of the solve's memory is proportional to the system);
 // a pipelined solve keeps a ring of such buffers within kRingBudget, so the
 // basis kernel of chunk k waits only for the eigensolver of chunk k - nbuf.
-// Unpipelined solves on the library's own buffers take a fifth of the device
-// memory that is free (counting the chunk buffer they already hold), between
+// A solve that runs its chunks in sequence because its kernel does (nobody asked
+// for it) has one buffer of that size.  Where the caller or a tuning asked, the buffer takes a
+// fifth of the device memory that is free (counting the chunk buffer held already), between
 // 4 and 64 GiB: fewer, longer chunks lose less to each chunk's drain (on the
 // 262,144-atom cell 60 chunks of 4 GiB cost 4.6 % over 4 of 65 GB); a
 // caller's workspace and size queries keep 4 GiB so that the two agree.
@@ -1123,8 +1124,9 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     // unit, so that no eigensolver runs beside them: chunks in sequence (4,096
     // sp3 atoms 16.8 ms, pipelined 17.3 ms).  Beside the atom kernel one costs
     // more than it hides (2,048 spd atoms, nu = 30, FP64: 97 ms, pipelined 159).
+    const bool pipe_asked = opts.pipeline >= 0 || (tn && tn->pipe >= 0);
     const int pipe = opts.pipeline >= 0 ? opts.pipeline
-                     : tn && tn->pipe >= 0 ? tn->pipe : resident || want_kernel == MA_BASIS_ATOM ? 0 : 4;
+                     : pipe_asked ? tn->pipe : resident || want_kernel == MA_BASIS_ATOM ? 0 : 4;
     P.kind = resident ? ma::kBasisResident
              : want_kernel == MA_BASIS_ONCHIP ? ma::kBasisOnchip
              : want_kernel == MA_BASIS_GROUP ? ma::kBasisGroup
@@ -1195,7 +1197,10 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     size_t mid_budget = src->limited ? src->cap / 4 : kMidBudget;
     if (!src->region() && pipe < 2) {   // (a pipelined ring keeps 4 GiB buffers)
         size_t fr = 0, tot = 0;
-        if (hipMemGetInfo(&fr, &tot) == hipSuccess)
+        if (!pipe_asked)
+            mid_budget = kRingBudget;
+        else if (sizeof(double) * (size_t)J.mid_stride * ncols > kMidBudget &&
+                 hipMemGetInfo(&fr, &tot) == hipSuccess)
             mid_budget = std::min(kMidBudgetMax, std::max(kMidBudget, (fr + ctx->mid.bytes) / 5));
     }
     const int64_t per_chunk = std::max<int64_t>(o, (int64_t)(mid_budget / (sizeof(double) * J.mid_stride)));

@@ -129,3 +129,28 @@ def test_dos_without_memory_for_its_partial_sums(env):
         torch.cuda.empty_cache()
     assert np.abs(got - want).max() <= 1e-12 * want.max()
     ctx.close()
+
+
+def test_chunk_buffer_of_the_default(env):
+    """43,200 columns of 64 vectors fill 11 GB of chunk buffer; by default a solve keeps
+    at most 8 GiB of it, whatever is free, and gives the same as one long chunk."""
+    torch, ma = env
+    s = synth.config_fcc_spd(5, cells=(10, 10, 12))
+    p = q = 32
+    rho, ref = (torch.zeros(s.nblk * 81, dtype=torch.float64, device="cuda") for _ in range(2))
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    # (basis workspaces, lists and a chunk buffer of 4 GiB)
+    size = ctx.workspace_size(None, p, q, mu=0.3, opts=ma.default_opts())
+    assert size == ctx.workspace_size(None, p, q, mu=0.3, opts=ma.default_opts(basis_kernel="atom", pipeline=0))
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    print(f"[gpu-case] {s.M} columns, p = q = 32", flush=True)
+    a = ctx.solve_columns(None, p, q, mu=0.3, kT=s.kT, rho=rho)
+    grown = before - torch.cuda.mem_get_info()[0]
+    b = ctx.solve_columns(None, p, q, mu=0.3, kT=s.kT, rho=ref, opts=ma.default_opts(pipeline=0))
+    print(f"[gpu-case] {grown / MB:.0f} MB, in a workspace {size / MB:.0f}", flush=True)
+    # (1 GiB for what the runtime keeps for itself)
+    assert grown <= size + 5 * 1024 * MB
+    assert torch.equal(rho, ref) and a.energy == b.energy
+    ctx.close()
