@@ -225,7 +225,8 @@ typedef struct {
     int32_t tried_slots[64];
     int32_t tried_schedule[64];
     double tried_ms[64];        /* whole-solve device time of each candidate (best of reps) */
-    int32_t basis_kernel;       /* chosen: MA_BASIS_ONCHIP, _WORKSPACE, _GROUP or _ATOM */
+    int32_t basis_kernel;       /* chosen: MA_BASIS_ONCHIP, _WORKSPACE, _GROUP or _ATOM,
+                                   or MA_BASIS_AUTO (see ma_autotune) */
     int32_t tried_kernel[64];
     int32_t pipeline;           /* chosen: the pipeline option of the solve (0 = off) */
     int32_t tried_pipeline[64];
@@ -427,7 +428,9 @@ MA_API ma_status ma_mlp_train_step(ma_ctx *ctx, const float *x, const float *t, 
 
 /* Autotuner of the launch (not part of the paper's method, which runs the
  * columns of Sec. 2 independently): time the solve on cols[0..ncols) (NULL = all) for every
- * candidate -- basis kernel (each one that can hold the shape) x
+ * candidate -- basis kernel (each one that can hold the shape, and the automatic
+ * choice, as MA_BASIS_AUTO, where that is MA_BASIS_ONCHIP in its register form but the
+ * named kernel cannot hold the shape) x
  * slots per CU from 1 to that kernel's occupancy limit x every schedule, with
  * the pipeline option of opts (-1: 4), and each kernel's fastest slots per
  * CU again with pipelining off, every schedule --
@@ -445,7 +448,8 @@ MA_API ma_status ma_autotune(ma_ctx *ctx, int64_t ncols, const int32_t *cols, in
 
 /* Store a previously found launch tuning for (p, q, precision) (e.g. from a cache);
  * basis_kernel is MA_BASIS_ONCHIP, MA_BASIS_WORKSPACE, MA_BASIS_GROUP or MA_BASIS_ATOM
- * (MA_BASIS_AUTO keeps the automatic choice); pipeline as in ma_opts (-1: 4). */
+ * (MA_BASIS_AUTO keeps the automatic choice); pipeline as in ma_opts (-1: the
+ * default there). */
 MA_API ma_status ma_set_tuning(ma_ctx *ctx, int32_t p, int32_t q, int32_t precision,
                                int32_t slots_per_cu, int32_t schedule, int32_t basis_kernel,
                                int32_t pipeline);

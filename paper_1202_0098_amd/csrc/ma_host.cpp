@@ -976,6 +976,23 @@ struct BufSource {
     }
 };
 
+// Whether the on-chip kernel's resident form holds the shape, with at most so many
+// operator blocks per row of the largest region.  It holds two of a row's blocks and
+// loads the others again for every product, from memory where the columns in flight
+// lie far apart.  Against the workspace kernel (the automatic choice otherwise), 480
+// orbitals, p = q = 8 and 4,000 columns in random order: 4.2 blocks per row 1.21 times
+// as fast, 8.8 0.99, 12 0.95 and 0.86 with p + q = 6 (whole cells in order: 1.15 at 12,
+// 0.71 at 40).  Against the LDS form (the named on-chip kernel otherwise), 2,000 columns,
+// p + q = 6: 1.5 times at 12, 0.99 at 19, 0.83 at 28.
+constexpr int kAutoRowBlocks = 8, kOnchipRowBlocks = 18;
+
+bool resident_fits(const ma_ctx *ctx, int nu, int q, int precision, int64_t row_blocks)
+{
+    return ctx->max_lnnz <= row_blocks * ctx->max_nat &&
+           ma::basis_resident_fits(ctx->nmax, nu, q, ctx->o, precision,
+                                   ma::lidx_bytes(ctx->max_nat, (int)ctx->max_lnnz));
+}
+
 ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, int32_t q,
                     double mu, double kT, const ma_opts *opts_in, double *rho, double *pi,
                     double *eps, double *wts, int32_t *col_stats, float *sj_near,
@@ -1030,7 +1047,8 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     if (sj_near && !ctx->have_geo) return ctx->fail(MA_EINVAL, "sj_near needs positions");
 
     // launch configuration: explicit, autotuned, or defaults
-    const ma_ctx::Tune *tn = ctx->find_tune(p, q, opts.precision);
+    // (the autotuner's trials give everything that a tuning would)
+    const ma_ctx::Tune *tn = slots_override > 0 ? nullptr : ctx->find_tune(p, q, opts.precision);
     P.sched = sched_override >= 0 ? sched_override
               : opts.schedule >= 0 ? opts.schedule : (tn ? tn->sched : MA_SCHED_LPT);
     ma::DevSystem &S = P.S;
@@ -1068,22 +1086,11 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     // kernel's resident form where it holds the shape (4,000 columns of 480
     // orbitals, nu = 30: basis 3.1 ms against 4.5), else the workspace kernel.
     // On-chip means the resident form wherever that holds the shape.
-    //
-    // Both up to a number of operator blocks per row of the largest region: the
-    // resident form holds two of a row's blocks and loads the others again for every
-    // product, from memory where the columns in flight lie far apart.  Against the
-    // workspace kernel, 480 orbitals, p = q = 8 and 4,000 columns in random order: 4.2
-    // blocks per row 1.21 times as fast, 8.8 0.99, 12 0.95 and 0.86 with p + q = 6
-    // (whole cells in order: 1.15 at 12, 0.71 at 40).  Against the LDS form, 2,000
-    // columns, p + q = 6: 1.5 times at 12, 0.99 at 19, 0.83 at 28.
-    constexpr int kAutoRowBlocks = 8, kOnchipRowBlocks = 18;
-    auto rows_at_most = [&](int64_t blocks) { return ctx->max_lnnz <= blocks * ctx->max_nat; };
     int want_kernel = opts.basis_kernel;
     if (want_kernel == MA_BASIS_AUTO && tn) want_kernel = tn->kernel;
-    const bool resident = ((want_kernel == MA_BASIS_AUTO && rows_at_most(kAutoRowBlocks)) ||
-                           (want_kernel == MA_BASIS_ONCHIP && fits && rows_at_most(kOnchipRowBlocks))) &&
-                          ma::basis_resident_fits(ctx->nmax, P.nu, q, ctx->o, opts.precision,
-                                                  ma::lidx_bytes(ctx->max_nat, (int)ctx->max_lnnz));
+    const bool resident =
+        (want_kernel == MA_BASIS_AUTO && resident_fits(ctx, P.nu, q, opts.precision, kAutoRowBlocks)) ||
+        (want_kernel == MA_BASIS_ONCHIP && fits && resident_fits(ctx, P.nu, q, opts.precision, kOnchipRowBlocks));
     // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of 630
     // orbitals, nu = 30: 23.6 ms against 42.2 (1.5 to 2.6 times at 500 to 864
     // atoms and nu = 1 to 48).  It runs one workgroup per atom, so it needs the
@@ -2048,8 +2055,14 @@ MA_API ma_status ma_autotune(ma_ctx *ctx, int64_t ncols, const int32_t *cols, in
         }
         return MA_OK;
     };
-    for (int kern = MA_BASIS_ONCHIP; kern <= MA_BASIS_ATOM; ++kern) {
-        if (kern == MA_BASIS_ONCHIP && !ma::basis_small_fits(ctx->nmax, p + q, q, ctx->o)) continue;
+    // The automatic choice is tried itself where it is a kernel that no name admits: the
+    // on-chip kernel's register form holds shapes (q > 16, or q > 8 with p + q <= 16)
+    // that the named kernel's LDS form does not.
+    const bool onchip = ma::basis_small_fits(ctx->nmax, p + q, q, ctx->o);
+    const bool automatic = !onchip && resident_fits(ctx, p + q, q, o.precision, kAutoRowBlocks);
+    for (int kern = MA_BASIS_AUTO; kern <= MA_BASIS_ATOM; ++kern) {
+        if (kern == MA_BASIS_AUTO && !automatic) continue;
+        if (kern == MA_BASIS_ONCHIP && !onchip) continue;
         if (kern == MA_BASIS_GROUP && !ma::basis_group_fits(ctx->nmax, p + q, ctx->o)) continue;
         if (kern == MA_BASIS_ATOM && !ma::basis_atom_fits(ctx->nmax, p + q, ctx->o, o.precision)) continue;
         o.basis_kernel = kern;

@@ -64,3 +64,43 @@ def test_dense_operators_leave_the_register_form(env, rcut, rows, onchip):
         got = _solve(torch, ma, ctx, s, 6, 5, kernel, cols).reshape(-1, 4, 4)
         assert np.abs(got - want).max() <= 1e-10     # the parity tests' FP64 bound
     ctx.close()
+
+
+@pytest.mark.parametrize("p,q", [(5, 11), (15, 17), (10, 18)])
+def test_tuner_tries_what_runs_untuned(env, p, q):
+    """Shapes that the on-chip kernel holds in its register form alone: the tuner tries
+    the automatic choice (whatever an earlier tuning says), and a solve with the tuning
+    it finds takes it, as an untuned one does.  By name the kernel stays refused."""
+    torch, ma = env
+    import oracle
+    s = _sp3((4, 4, 4), 100)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    untuned = _size(ma, ctx, None, p, q, "auto")
+    assert untuned < _size(ma, ctx, None, p, q, "workspace")
+    with pytest.raises(ma.MarnoldiError) as ei:
+        _size(ma, ctx, None, p, q, "onchip")
+    assert ei.value.status == ma.MA_EINVAL
+    ctx.set_tuning(p, q, "fp64", 1, "lpt", "workspace", 0)
+    print(f"[gpu-case] autotune p={p} q={q}", flush=True)
+    t = ctx.autotune(None, p, q, mu=0.9, kT=s.kT, reps=2)
+    assert {k for _, _, _, k in t["tried"]} >= {"auto", "workspace"}
+    # (1.2 to 1.9 times the workspace kernel's speed)
+    assert t["basis_kernel"] == "auto"
+    assert _size(ma, ctx, None, p, q, "auto") == untuned
+    got = _solve(torch, ma, ctx, s, p, q, "auto").reshape(-1, 4, 4)
+    cols = np.arange(8, dtype=np.int32)
+    raw = oracle.solve_raw(s, cols=cols, p=p, q=q)
+    want = oracle.scatter_slots(s, cols, oracle.outputs(s, raw, 0.9, s.kT)[0])
+    assert np.abs(got[:s.blk_ptr[2]] - want[:s.blk_ptr[2]]).max() <= 1e-10
+    ctx.close()
+
+
+def test_tuner_names_the_kernels_that_have_one(env):
+    torch, ma = env
+    s = _sp3((3, 3, 3), 60)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    t = ctx.autotune(None, 6, 5, mu=0.9, kT=s.kT, reps=1)
+    assert "onchip" in {k for _, _, _, k in t["tried"]} and "auto" not in {k for _, _, _, k in t["tried"]}
+    ctx.close()
