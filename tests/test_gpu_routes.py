@@ -104,3 +104,49 @@ def test_tuner_names_the_kernels_that_have_one(env):
     t = ctx.autotune(None, 6, 5, mu=0.9, kT=s.kT, reps=1)
     assert "onchip" in {k for _, _, _, k in t["tried"]} and "auto" not in {k for _, _, _, k in t["tried"]}
     ctx.close()
+
+
+# 256 and 512 orbitals, 16 and 32 vectors, one more of each; chains that LDS does not hold
+@pytest.mark.parametrize("atoms,p,q,onchip", [
+    (64, 8, 8, True), (64, 9, 8, True), (65, 8, 8, True), (64, 16, 16, True), (64, 1, 31, True),
+    (64, 17, 16, False), (128, 16, 16, True), (128, 8, 8, True), (128, 17, 16, False),
+    (129, 8, 8, False), (128, 8, 24, True), (128, 1, 31, False)])
+def test_shapes_of_the_register_form(env, atoms, p, q, onchip):
+    torch, ma = env
+    s = _sp3((4, 4, 4), atoms)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    # (without a basis workspace: less than the workspace kernel by all of its own, of
+    # which a workgroup's is 3 nu + q vectors)
+    auto, work = (_size(ma, ctx, None, p, q, k) for k in ("auto", "workspace"))
+    if onchip:
+        assert auto <= work - 256 * (3 * (p + q) + q) * 4 * atoms * 8
+    else:
+        assert auto == work
+    ctx.close()
+
+
+@pytest.mark.parametrize("which,kernel", [("all", "atom"), ("eight", "atom"), ("seven", "atom"),
+                                          ("shuffled", "atom"), ("six", "workspace"),
+                                          ("255 atoms", "workspace"), ("256 atoms", "atom")])
+def test_columns_that_take_the_atom_kernel(env, which, kernel):
+    """FP64 spd: at least 256 atoms and on average 7 columns of each."""
+    torch, ma = env
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    s = synth.config_fcc_spd(5, cells=(4, 4, 5))
+    per = {"eight": 8, "seven": 7, "six": 6}.get(which, 9)
+    cols = np.array([9 * a + i for a in range(s.n_atoms) for i in range(per)], np.int32)
+    if which == "shuffled":
+        cols = np.random.default_rng(1).permutation(cols).astype(np.int32)
+    if which.endswith("atoms"):
+        cols = cols[:9 * int(which.split()[0])]
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    size = {k: _size(ma, ctx, cols, 4, 3, k) for k in ("auto", "atom", "workspace")}
+    assert size["atom"] > size["workspace"] and size["auto"] == size[kernel]
+    # not where the caller chose, nor in the mixed modes
+    for kw in (dict(basis_kernel="workspace"), dict(precision="mixed_f64acc")):
+        a, b = (ctx.workspace_size(cols, 4, 3, mu=0.3, opts=ma.default_opts(pipeline=0, **{**kw, **x}))
+                for x in ({}, dict(basis_kernel="workspace")))
+        assert a == b
+    ctx.close()
