@@ -397,10 +397,10 @@ hipError_t launch_map_sj(int ncols, const int32_t *cols, int o, RegionView cur, 
     return hipGetLastError();
 }
 
-// Up to 16 values per block (o <= 4) and 24,576 blocks one launch: 4,096 sp3 atoms
-// (20,480 blocks) 38.2 us with the call's synchronisation, in two launches 41.5;
-// 5,832 atoms in two 40.0, by one wavefront per atom 45.8.
-bool forces_need_blocks(int o, int64_t nblk) { return o > 4 || nblk > 24576; }
+// Up to 16 values per block (o <= 4) and 16,384 blocks one launch (fastest call of
+// 3,000, with its synchronisation: 1,000 sp3 atoms 22.0 us, in two launches 24.3; 2,744
+// atoms, 13,720 blocks, 24.6 either way; 4,096 atoms 26.1 and 24.9).
+bool forces_need_blocks(int o, int64_t nblk) { return o > 4 || nblk > 16384; }
 
 hipError_t launch_forces(int n_atoms, int o, const int64_t *blk_ptr, const int32_t *blk_col,
                          const int32_t *blk_t, const double *dH, const double *dS,

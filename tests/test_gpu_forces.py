@@ -1,4 +1,4 @@
-"""The force kernels alone, on every route: one launch (o <= 4, up to 24,576 blocks),
+"""The force kernels alone, on every route: one launch (o <= 4, up to 16,384 blocks),
 and block sums first, with 16 lanes and a wavefront per atom, for several o.
 
 Random blocks against extended precision.  Sums of products whose additions lose
