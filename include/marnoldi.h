@@ -132,9 +132,10 @@ typedef struct {
                                while the configuration and buffers are unchanged */
     int32_t basis_kernel;   /* MA_BASIS_AUTO: the autotuned kernel for (p, q, precision)
                                if ma_autotune ran, else MA_BASIS_ONCHIP in its register
-                               form (MA_PREC_FP64, o = 4, regions of at most 512
-                               orbitals and 8 operator blocks per row, p + q <= 32);
-                               MA_BASIS_ATOM (MA_PREC_FP64,
+                               form (MA_PREC_FP64, o = 4, p + q <= 32, regions of at
+                               most 512 orbitals and 8 operator blocks per row, and LDS
+                               for q vectors and the largest region's index: up to
+                               q = 25 at 512 orbitals); MA_BASIS_ATOM (MA_PREC_FP64,
                                o = 9, at least as many atoms as compute units and on
                                average 7 columns of each, and its workspaces fit);
                                else MA_BASIS_WORKSPACE.
@@ -143,7 +144,9 @@ typedef struct {
                                basis vector.
                                MA_BASIS_ONCHIP: one column per workgroup, basis in LDS
                                and registers (regions of at most 512 orbitals,
-                               p + q <= 32, q <= 16; q <= 8 when p + q <= 16).
+                               p + q <= 32, q <= 16; q <= 8 when p + q <= 16), in the
+                               register form where that holds the shape, up to 18
+                               operator blocks per row.
                                MA_BASIS_GROUP: the requested columns of one atom in
                                lockstep, one SpMM per step for all of them (o = 4 or
                                9).
@@ -167,9 +170,9 @@ typedef struct {
                                stream beside the later basis kernels, with a ring of
                                chunk buffers of at most 8 GiB; 0 or 1: off (chunks in
                                sequence on one stream); -1 (default): the autotuned
-                               choice for (p, q, precision) if ma_autotune ran, else 4
-                               (0 where the kernel is MA_BASIS_ATOM or the automatic
-                               one is MA_BASIS_ONCHIP) */
+                               choice for (p, q, precision) if ma_autotune ran, else 4,
+                               or 0 where the kernel is MA_BASIS_ATOM or the register
+                               form of MA_BASIS_ONCHIP */
     int32_t keep_sj;        /* 1: keep each solved column's s_j = S_A^-1 e_j (region
                                vector, FP64, M * nmax doubles in all) for a later solve
                                with MA_START_PREVIOUS; the kept set belongs to the
@@ -432,7 +435,7 @@ MA_API ma_status ma_mlp_train_step(ma_ctx *ctx, const float *x, const float *t, 
  * choice, as MA_BASIS_AUTO, where that is MA_BASIS_ONCHIP in its register form but the
  * named kernel cannot hold the shape) x
  * slots per CU from 1 to that kernel's occupancy limit x every schedule, with
- * the pipeline option of opts (-1: 4), and each kernel's fastest slots per
+ * the pipeline option of opts (-1: 4 in the trials), and each kernel's fastest slots per
  * CU again with pipelining off, every schedule --
  * `reps` times each at chemical potential mu (finite), and keep the fastest
  * configuration for this (p, q, opts->precision) in the context, except that

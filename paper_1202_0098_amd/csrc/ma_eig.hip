@@ -25,10 +25,10 @@ namespace {
 // What bounds it: instruction issue of the wavefront that runs the QL
 // rotations (about 1,060 per column at nu = 30); the matrix cores and memory
 // are idle.  Hence one wavefront per column up to nu = 32 (no barriers) and
-// v_rsq_f64 with one third-order correction in place of square roots and
-// divisions.  Against the kernel below with its matrices in LDS and IEEE square
-// roots: one column of nu = 30 210 us (553 us), 4,000 of them 627 us (1,462 us),
-// one of nu = 16 75 us (189 us).
+// v_rsq_f64 with one third-order correction (within 2 ulp) in place of square roots
+// and divisions.  Against the kernel below with its matrices in LDS and IEEE square
+// roots: one column of nu = 30 197 us (553 us), 4,000 of them 604 us (1,462 us),
+// one of nu = 16 67 us (189 us).
 constexpr int kEigWaves = 3;   // waves per SIMD that the registers leave room for
 
 template <int CW, int NG, int RM>
@@ -44,9 +44,9 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
     double *Z = Zm + LDZ;
     double2 *de = de_ + 1;
     __shared__ double xs[CW], ys[CW], gs[CW], lv[CW], bv_[CW], gv[CW];
-    __shared__ double ev[CW], vj[CW], svj[CW], fw[CW];
+    __shared__ double ev[CW], vj[CW], fw[CW];
     __shared__ double part[NWV > 1 ? 2 * NG * CW : 1];
-    __shared__ int rank[CW], inv[CW], s_status;
+    __shared__ int rank[CW], s_status;
     const int nu = J.nu, o = S.o;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int col = tid % CW, grp = tid / CW, row0 = grp * RPG;
@@ -309,9 +309,7 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
             }
             ev[col] = va;
             vj[col] = v1;
-            svj[col] = v2;
             rank[col] = rk;
-            inv[rk] = col;
             eps_o[rk] = va;
             wts_o[rk] = v1 * v2;
         } else {
@@ -439,11 +437,10 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
     // factor of S~ lives in the Z area until Z is needed, waits in the S~
     // slot of the chunk buffer meanwhile, and comes back for C = Lc^-T Z.
     double *A = smem, *Z = smem + nu * nu, *B = Z;
-    double *ev = smem + 2 * nu * nu, *vj = ev + nu, *svj = vj + nu, *fw = svj + nu;
-    double *hh = fw + nu, *ee = hh + nu, *rd = ee + nu;
+    double *ev = smem + 2 * nu * nu, *vj = ev + nu, *svj = vj + nu;
+    double *hh = svj + nu, *ee = hh + nu, *rd = ee + nu;
     double *upj = rd + nu;   // 2 nu
     int *rank = reinterpret_cast<int *>(upj + 2 * nu);
-    int *inv = rank + nu;
     __shared__ double hv[kMaxNu];   // current Householder vector (separate objects: the
     __shared__ double hq[kMaxNu];   // compiler may keep their loads ahead of A's stores)
     const int lane = threadIdx.x;
@@ -747,7 +744,6 @@ __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
             if (a < L) {
                 eps_o[rank[a]] = ev[a];
                 wts_o[rank[a]] = vj[a] * svj[a];
-                inv[rank[a]] = a;
             } else {
                 eps_o[a] = NAN;
                 wts_o[a] = 0.0;
@@ -817,8 +813,8 @@ hipError_t launch_eig(const DevSystem &S, const DevJob &J, hipStream_t st)
 {
     if (J.cn < 1) return hipSuccess;
     if (J.precision != 0 && !J.direct) {
-        const size_t smem = sizeof(double) * (2 * (size_t)J.nu * J.nu + 10 * (size_t)J.nu) +
-                            sizeof(int) * 2 * (size_t)J.nu;
+        const size_t smem = sizeof(double) * (2 * (size_t)J.nu * J.nu + 8 * (size_t)J.nu) +
+                            sizeof(int) * (size_t)J.nu;
         hipError_t e = hipFuncSetAttribute((const void *)k_eig_f32,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;

@@ -895,7 +895,6 @@ MA_API int64_t ma_region_atoms(const ma_system *sys, const ma_region *reg, int32
 
 namespace {
 
-// Everything one launch sequence needs, resolved from the arguments.
 // What the host reads after a solve, in one copy.
 struct Readback {
     int ctl[16];       // queue counters, then the first failed column and a counter
@@ -905,6 +904,7 @@ struct Readback {
 };
 static_assert(sizeof(Readback) == 128 && ma::kMaxQueues + 2 <= 16, "layout");
 
+// Everything one launch sequence needs, resolved from the arguments.
 struct Plan {
     ma_opts opts;
     int p = 0, q = 0, nu = 0, slots = 0, sched = 0;
@@ -1084,17 +1084,17 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
                          "orbitals, precision %d)", ctx->o, ctx->nmax, opts.precision);
     // Automatic choice: the autotuned kernel if there is one, else the on-chip
     // kernel's resident form where it holds the shape (4,000 columns of 480
-    // orbitals, nu = 30: basis 3.1 ms against 4.5), else the workspace kernel.
+    // orbitals, nu = 30: basis 3.0 ms against 4.5), else the workspace kernel.
     // On-chip means the resident form wherever that holds the shape.
     int want_kernel = opts.basis_kernel;
     if (want_kernel == MA_BASIS_AUTO && tn) want_kernel = tn->kernel;
     const bool resident =
         (want_kernel == MA_BASIS_AUTO && resident_fits(ctx, P.nu, q, opts.precision, kAutoRowBlocks)) ||
         (want_kernel == MA_BASIS_ONCHIP && fits && resident_fits(ctx, P.nu, q, opts.precision, kOnchipRowBlocks));
-    // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of 630
-    // orbitals, nu = 30: 23.6 ms against 42.2 (1.5 to 2.6 times at 500 to 864
+    // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of up to 774
+    // orbitals, nu = 30: 22.9 ms against 42.5 (1.5 to 2.6 times at 500 to 864
     // atoms and nu = 1 to 48).  It runs one workgroup per atom, so it needs the
-    // atoms to fill the chip (256 atoms: 16.2 against 20.1 ms) and most columns
+    // atoms to fill the chip (256 atoms: 15.3 against 19.6 ms) and most columns
     // of each (7 of 9: 1.1 to 1.6 times, 5 of 9: 0.9 to 1.4, 2 of 9: 0.5 to 0.8).
     // For o = 4 the workspace kernel is faster (3,001 atoms of up to 1,040
     // orbitals, nu = 40: 35 ms against 57).
@@ -1129,7 +1129,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         want_kernel = MA_BASIS_WORKSPACE;
     // The resident kernel's workgroups take every register of their compute
     // unit, so that no eigensolver runs beside them: chunks in sequence (4,096
-    // sp3 atoms 16.8 ms, pipelined 17.3 ms).  Beside the atom kernel one costs
+    // sp3 atoms 14.4 ms, pipelined 15.2).  Beside the atom kernel one costs
     // more than it hides (2,048 spd atoms, nu = 30, FP64: 97 ms, pipelined 159).
     const bool pipe_asked = opts.pipeline >= 0 || (tn && tn->pipe >= 0);
     const int pipe = opts.pipeline >= 0 ? opts.pipeline

@@ -227,7 +227,8 @@ hipError_t launch_rho(const DevSystem &S, const DevJob &J, const double *mu_ptr,
 {
     const int grid = J.ncols < 65536 ? J.ncols : 65536;
     // rows of amplitudes per stage: 128 (one per pair of lanes) while they fit
-    // 32 KB, which leaves room for five workgroups on a compute unit
+    // 32 KB, which with the factors leaves room for four workgroups on a compute
+    // unit (five up to nu = 31 in FP64)
     const size_t row = J.nu * (J.precision == 0 ? sizeof(double) : sizeof(float));
     const int rows = (int)std::min<size_t>(std::min(128, S.maxpat), std::max<size_t>(1, 32 * 1024 / row));
     // one wavefront per column where a pass of it holds the rows (16,384 columns

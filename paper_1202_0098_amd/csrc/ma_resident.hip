@@ -33,8 +33,8 @@
 // What bounds it: instruction issue (two wavefronts per SIMD, about a thousand
 // instructions per step and wavefront) and the round trips between phases; its
 // memory traffic is the operator and the outputs.  Measured against the workspace
-// kernel, nu = 30, 480 orbitals: one column 200 us (398), 4,000 columns 3.1 ms
-// (4.5), 16,384 columns 12.5 ms (17.1); nu = 16, 256 orbitals: 82 us (149).
+// kernel, nu = 30, 480 orbitals: one column 187 us (383), 4,000 columns 3.0 ms
+// (4.5), 16,384 columns 12.1 ms (17.0); nu = 16, 256 orbitals: one column 76 us (132).
 // A form with the vectors spread over the wavefronts (partial combinations
 // through LDS) and one with U row-owned and scalar-broadcast coefficients took
 // 463 and 278 us per column.
@@ -53,8 +53,9 @@ namespace {
 // the vectors they meet are complete, and S's are held for a step's second
 // product; absent blocks point at the zero rows past the vectors' end, so that a
 // product needs no selects.  KEEP = 2: each block of both operators holds 32
-// registers beside the 128 of U, and three or more spill (a 4,000-column solve
-// 4.68 ms, 4.73 with three, 6.79 with all five of a crystal's row).
+// registers beside the 128 of U; two take the last of them and 64 bytes per lane of
+// scratch, three or more spill more than they save (a 4,000-column solve 4.68 ms, 4.73
+// with three, 6.79 with all five of a crystal's row).
 template <int O>
 struct Row {
     static constexpr int KEEP = 2;
@@ -73,16 +74,12 @@ struct Row {
 template <int O>
 __device__ __forceinline__ void entries(const double *x, int atom, double (&v)[O])
 {
-    if constexpr (O % 2 == 0) {
+    static_assert(O % 2 == 0, "pairs");
 #pragma unroll
-        for (int c = 0; c < O; c += 2) {
-            const double2 w = *reinterpret_cast<const double2 *>(x + atom * O + c);
-            v[c] = w.x;
-            v[c + 1] = w.y;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < O; ++c) v[c] = x[atom * O + c];
+    for (int c = 0; c < O; c += 2) {
+        const double2 w = *reinterpret_cast<const double2 *>(x + atom * O + c);
+        v[c] = w.x;
+        v[c + 1] = w.y;
     }
 }
 
