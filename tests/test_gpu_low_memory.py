@@ -21,17 +21,35 @@ def env():
     yield torch, ma
 
 
-def _hold(torch, leave):
-    """Device memory of the caller's, so that `leave` bytes are free (what the runtime
-    says is free grows by some of its own when a large piece is taken: twice)."""
+def _take(torch, size):
+    return torch.empty(size, dtype=torch.uint8, device="cuda")
+
+
+def _hold_about(torch, leave):
+    """Device memory of the caller's, so that about `leave` bytes are free (to within a
+    GB: what the runtime says is free is not just what it gives)."""
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     held = []
     for _ in range(3):
-        more = (torch.cuda.mem_get_info()[0] - leave) // (2 * MB) * (2 * MB)
-        if more > 0:
-            held.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
-    assert abs(torch.cuda.mem_get_info()[0] - leave) <= 8 * MB
+        more = torch.cuda.mem_get_info()[0] - leave
+        if more > MB:
+            held.append(_take(torch, more))
+    return held
+
+
+def _hold_all(torch, leave):
+    """All that the runtime gives but `leave` bytes, a few MB."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    room, held, size = _take(torch, leave), [], torch.cuda.mem_get_info()[0]
+    while size >= MB:
+        try:
+            held.append(_take(torch, size))
+        except RuntimeError:
+            size //= 2
+    del room
+    torch.cuda.empty_cache()
     return held
 
 
@@ -40,21 +58,20 @@ def test_automatic_kernel_where_its_other_buffers_do_not_fit(env):
     solve's buffers beside them; the workspace kernel's do."""
     torch, ma = env
     s = synth.config_fcc_spd(5, cells=(8, 8, 12))
-    p, q, n = 4, 3, s.nblk * 81
+    p, q, n = 28, 20, s.nblk * 81
     opts = {k: ma.default_opts(basis_kernel=k, pipeline=0, slots_per_cu=1) for k in ("auto", "atom", "workspace")}
-    rho = torch.zeros(n, dtype=torch.float64, device="cuda")
-    ref = torch.zeros_like(rho)
+    rho, ref, by_atoms = (torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(3))
     ctx = ma.Context(0)
     ctx.build_tb(s)
-    ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["atom"])   # (kernels loaded)
+    ctx.solve_columns(None, p, q, kT=s.kT, rho=by_atoms, opts=opts["atom"])
     want = ctx.solve_columns(None, p, q, kT=s.kT, rho=ref, opts=opts["workspace"])
     ctx.close()
     ctx = ma.Context(0)
     ctx.build_tb(s)
     auto, atom, work = (ctx.workspace_size(None, p, q, opts=opts[k]) for k in ("auto", "atom", "workspace"))
-    leave = atom - 200 * MB
-    assert auto == atom and work + 100 * MB <= leave
-    held = _hold(torch, leave)
+    leave = (atom + work) // 2
+    assert auto == atom and atom - work >= 2000 * MB
+    held = _hold_about(torch, leave)
     try:
         print(f"[gpu-case] {leave / MB:.0f} MB free, atom {atom / MB:.0f}, workspace {work / MB:.0f}",
               flush=True)
@@ -65,8 +82,8 @@ def test_automatic_kernel_where_its_other_buffers_do_not_fit(env):
         torch.cuda.empty_cache()
     assert torch.equal(rho, ref) and got.mu == want.mu and got.energy == want.energy
     # with the memory back, the atom kernel again
-    got = ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["auto"])
-    assert float((rho - ref).abs().max()) <= 1e-10     # the parity tests' bound between kernels
+    ctx.solve_columns(None, p, q, kT=s.kT, rho=rho, opts=opts["auto"])
+    assert torch.equal(rho, by_atoms) and not torch.equal(rho, ref)
     ctx.close()
 
 
@@ -91,8 +108,8 @@ def test_forces_without_memory_for_the_block_sums(env, kind):
         ctx.build_tb(s)
         held = []
         if out is F:   # the sums take 48 bytes per block
-            held = _hold(torch, 4 * MB)
-            assert 48 * s.nblk > torch.cuda.mem_get_info()[0]
+            held = _hold_all(torch, 4 * MB)
+            assert 48 * s.nblk > 4 * MB
         print(f"[gpu-case] forces, {s.nblk} blocks, {torch.cuda.mem_get_info()[0] / MB:.0f} MB free", flush=True)
         try:
             ctx.forces(dH, dS, rho, pi, out)
@@ -104,8 +121,8 @@ def test_forces_without_memory_for_the_block_sums(env, kind):
 
 
 def test_dos_without_memory_for_its_partial_sums(env):
-    """2,048 energies and 245,760 Ritz pairs in 240 chunks take 3.9 MB of partial sums, in
-    30 chunks 0.5.  The two groupings agree to the rounding of sums of 245,760
+    """8,192 energies and 245,760 Ritz pairs in 240 chunks take 15.7 MB of partial sums, in
+    30 chunks 2.  The two groupings agree to the rounding of sums of 245,760
     positive terms (their weights are: an orthonormal basis), each of which is at
     most 8,192 long before it is added: 8192 x 2^-53 = 1e-12."""
     torch, ma = env
@@ -113,15 +130,15 @@ def test_dos_without_memory_for_its_partial_sums(env):
     ctx = ma.Context(0)
     ctx.build_tb(s)
     ctx.solve_columns(None, 10, 5, mu=0.9, kT=s.kT)
-    E = np.linspace(-16.0, 14.0, 2048)
+    E = np.linspace(-16.0, 14.0, 8192)
     ref = ma.Context(0)
     ref.build_tb(s)
     ref.solve_columns(None, 10, 5, mu=0.9, kT=s.kT)
     want = ref.dos(E, 0.1)
     ref.close()
-    held = _hold(torch, 2 * MB)
+    held = _hold_all(torch, 8 * MB)
     try:
-        assert torch.cuda.mem_get_info()[0] < 240 * 2048 * 8
+        assert 8 * MB < 240 * 8192 * 8
         print(f"[gpu-case] dos, {torch.cuda.mem_get_info()[0] / MB:.0f} MB free", flush=True)
         got = ctx.dos(E, 0.1)
     finally:
