@@ -2,6 +2,8 @@
 falls back to the one that fits, the forces to one launch without block sums, the density
 of states to fewer partial sums."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -21,10 +23,6 @@ def env():
     yield torch, ma
 
 
-def _take(torch, size):
-    return torch.empty(size, dtype=torch.uint8, device="cuda")
-
-
 def _hold_about(torch, leave):
     """Device memory of the caller's, so that about `leave` bytes are free (to within a
     GB: what the runtime says is free is not just what it gives)."""
@@ -33,24 +31,40 @@ def _hold_about(torch, leave):
     held = []
     for _ in range(3):
         more = torch.cuda.mem_get_info()[0] - leave
-        if more > MB:
-            held.append(_take(torch, more))
+        if more > 64 * MB:
+            held.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
     return held
 
 
-def _hold_all(torch, leave):
-    """All that the runtime gives but `leave` bytes, a few MB."""
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    room, held, size = _take(torch, leave), [], torch.cuda.mem_get_info()[0]
-    while size >= MB:
-        try:
-            held.append(_take(torch, size))
-        except RuntimeError:
-            size //= 2
-    del room
-    torch.cuda.empty_cache()
-    return held
+class _HoldAll:
+    """All that the runtime gives but `leave` bytes, a few MB, without torch's allocator
+    and its larger pieces."""
+
+    def __init__(self, torch, leave):
+        self.hip = ctypes.CDLL("libamdhip64.so")
+        self.hip.hipMalloc.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t]
+        self.hip.hipFree.argtypes = [ctypes.c_void_p]
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        room, size, self.held = self._take(leave), torch.cuda.mem_get_info()[0], []
+        while size >= 2 * MB:
+            ptr = self._take(size)
+            if ptr:
+                self.held.append(ptr)
+            else:
+                size = size // 2 // (2 * MB) * (2 * MB)
+        self.hip.hipFree(room)
+
+    def _take(self, size):
+        ptr = ctypes.c_void_p()
+        if self.hip.hipMalloc(ctypes.byref(ptr), size) == 0:
+            return ptr
+        self.hip.hipGetLastError()
+        return None
+
+    def release(self):
+        for ptr in self.held:
+            self.hip.hipFree(ptr)
 
 
 def test_automatic_kernel_where_its_other_buffers_do_not_fit(env):
@@ -106,16 +120,16 @@ def test_forces_without_memory_for_the_block_sums(env, kind):
     for out in (ref, F):
         ctx = ma.Context(0)
         ctx.build_tb(s)
-        held = []
+        held = None
         if out is F:   # the sums take 48 bytes per block
-            held = _hold_all(torch, 4 * MB)
-            assert 48 * s.nblk > 4 * MB
+            held = _HoldAll(torch, 4 * MB)
+            assert 48 * s.nblk > 8 * MB
         print(f"[gpu-case] forces, {s.nblk} blocks, {torch.cuda.mem_get_info()[0] / MB:.0f} MB free", flush=True)
         try:
             ctx.forces(dH, dS, rho, pi, out)
         finally:
-            del held
-            torch.cuda.empty_cache()
+            if held:
+                held.release()
         ctx.close()
     assert float((F - ref).abs().max()) <= 2 ** -52 * float(ref.abs().max())
 
@@ -136,14 +150,12 @@ def test_dos_without_memory_for_its_partial_sums(env):
     ref.solve_columns(None, 10, 5, mu=0.9, kT=s.kT)
     want = ref.dos(E, 0.1)
     ref.close()
-    held = _hold_all(torch, 8 * MB)
+    held = _HoldAll(torch, 10 * MB)
     try:
-        assert 8 * MB < 240 * 8192 * 8
         print(f"[gpu-case] dos, {torch.cuda.mem_get_info()[0] / MB:.0f} MB free", flush=True)
         got = ctx.dos(E, 0.1)
     finally:
-        del held
-        torch.cuda.empty_cache()
+        held.release()
     assert np.abs(got - want).max() <= 1e-12 * want.max()
     ctx.close()
 
