@@ -427,8 +427,9 @@ __global__ void __launch_bounds__(CW * NG, kEigWaves) k_eig(DevSystem S, DevJob 
 //   C = Lc^-T Z.
 // Every lane runs the scalar recurrences of the QL sweeps redundantly, so they
 // need no broadcasts.  Bound by instruction issue of the nine wavefronts that LDS
-// lets a compute unit hold: 62,208 columns of nu = 30 17.4 ms; with lanes masked
-// in the rotation loop 20.5, and with one lane per column in the updates too 22.0.
+// lets a compute unit hold at nu = 30: 62,208 columns 15.9 ms; with eight, 17.5; with
+// lanes masked in the rotation loop too, 20.5, and with one lane per column in the
+// updates, 22.0.
 __global__ void __launch_bounds__(64) k_eig_f32(DevSystem S, DevJob J)
 {
     extern __shared__ double smem[];
