@@ -138,7 +138,8 @@ typedef struct {
                                q = 25 at 512 orbitals); MA_BASIS_ATOM (MA_PREC_FP64,
                                o = 9, at least as many atoms as compute units and on
                                average 7 columns of each, and its workspaces fit);
-                               else MA_BASIS_WORKSPACE.
+                               else MA_BASIS_WORKSPACE (where its workspaces do not fit,
+                               the register form also past 8 blocks per row).
                                MA_BASIS_WORKSPACE: one column per workgroup, basis in a
                                device workspace, one dot sweep and one update sweep per
                                basis vector.

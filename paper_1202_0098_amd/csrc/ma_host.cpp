@@ -984,7 +984,7 @@ struct BufSource {
 // as fast, 8.8 0.99, 12 0.95 and 0.86 with p + q = 6 (whole cells in order: 1.15 at 12,
 // 0.71 at 40).  Against the LDS form (the named on-chip kernel otherwise), 2,000 columns,
 // p + q = 6: 1.5 times at 12, 0.99 at 19, 0.83 at 28.
-constexpr int kAutoRowBlocks = 8, kOnchipRowBlocks = 18;
+constexpr int kAutoRowBlocks = 8, kOnchipRowBlocks = 18, kAnyRowBlocks = INT_MAX;
 
 bool resident_fits(const ma_ctx *ctx, int nu, int q, int precision, int64_t row_blocks)
 {
@@ -997,7 +997,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
                     double mu, double kT, const ma_opts *opts_in, double *rho, double *pi,
                     double *eps, double *wts, int32_t *col_stats, float *sj_near,
                     int slots_override, int sched_override, Plan &P, BufSource *src = nullptr,
-                    bool auto_atom = true)
+                    bool second_choice = false)
 {
     BufSource own;
     if (!src) src = &own;
@@ -1088,8 +1088,9 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     // On-chip means the resident form wherever that holds the shape.
     int want_kernel = opts.basis_kernel;
     if (want_kernel == MA_BASIS_AUTO && tn) want_kernel = tn->kernel;
+    const bool automatic = want_kernel == MA_BASIS_AUTO;
     const bool resident =
-        (want_kernel == MA_BASIS_AUTO && resident_fits(ctx, P.nu, q, opts.precision, kAutoRowBlocks)) ||
+        (automatic && resident_fits(ctx, P.nu, q, opts.precision, second_choice ? kAnyRowBlocks : kAutoRowBlocks)) ||
         (want_kernel == MA_BASIS_ONCHIP && fits && resident_fits(ctx, P.nu, q, opts.precision, kOnchipRowBlocks));
     // FP64 solves of whole spd atoms take the atom kernel: 500 atoms of up to 774
     // orbitals, nu = 30: 22.9 ms against 42.5 (1.5 to 2.6 times at 500 to 864
@@ -1098,8 +1099,8 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
     // of each (7 of 9: 1.1 to 1.6 times, 5 of 9: 0.9 to 1.4, 2 of 9: 0.5 to 0.8).
     // For o = 4 the workspace kernel is faster (3,001 atoms of up to 1,040
     // orbitals, nu = 40: 35 ms against 57).
-    auto_atom = auto_atom && want_kernel == MA_BASIS_AUTO && !resident && afits && o == 9 &&
-                opts.precision == MA_PREC_FP64 && ncols >= 7 * (int64_t)ctx->cu_count;
+    bool auto_atom = automatic && !second_choice && !resident && afits && o == 9 &&
+                     opts.precision == MA_PREC_FP64 && ncols >= 7 * (int64_t)ctx->cu_count;
     if (auto_atom) {
         std::vector<char> seen(ctx->n_atoms, 0);
         int64_t atoms = 0;
@@ -1110,15 +1111,19 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         }
         auto_atom = atoms >= ctx->cu_count && ncols >= 7 * atoms;
     }
-    if (want_kernel == MA_BASIS_AUTO) want_kernel = auto_atom ? MA_BASIS_ATOM : MA_BASIS_WORKSPACE;
-    // (its workgroups' workspaces are larger: where they, or what the solve needs
-    // beside them, do not fit, the plan is made again with the workspace kernel)
-    auto without_atom = [&] {
+    if (automatic) want_kernel = auto_atom ? MA_BASIS_ATOM : MA_BASIS_WORKSPACE;
+    // Where the automatic choice, or what the solve needs beside it, does not fit, the
+    // plan is made again: with the workspace kernel instead of the atom kernel, whose
+    // workspaces are larger; with the register form, which has none, for the dense
+    // operators that it otherwise leaves to the workspace kernel.
+    const bool another = automatic && !second_choice &&
+                         (auto_atom || (!resident && resident_fits(ctx, P.nu, q, opts.precision, kAnyRowBlocks)));
+    auto plan_again = [&] {
         (void)hipGetLastError();
         src->off = src_off;
         P = Plan();
         return make_plan(ctx, ncols, cols, p, q, mu, kT, opts_in, rho, pi, eps, wts, col_stats, sj_near,
-                         slots_override, sched_override, P, src, false);
+                         slots_override, sched_override, P, src, true);
     };
     // the group kernel neither starts from nor keeps whole-region s_j
     const bool sj_io = opts.start == MA_START_PREVIOUS || opts.keep_sj;
@@ -1371,7 +1376,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
                 // as many persistent workgroups as the rest of the region holds
                 const size_t used = (src->off + 255) & ~(size_t)255;
                 const int64_t fit = used < src->cap ? (int64_t)((src->cap - used) / slot_bytes) : 0;
-                if (auto_atom && fit < P.slots) return without_atom();
+                if (another && fit < (auto_atom ? P.slots : 1)) return plan_again();
                 if (fit < 1)
                     return ctx->fail(MA_EINVAL, "the solve needs more than the %zu-byte scratch "
                                      "(%zu bytes before the first basis workspace of %zu bytes)",
@@ -1382,7 +1387,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         }
         P.bytes = (src->off + 255) & ~(size_t)255;
         if (src->size_only) return MA_OK;
-        if (src->off > src->cap && auto_atom) return without_atom();
+        if (src->off > src->cap && another) return plan_again();
         if (src->off > src->cap)
             return ctx->fail(MA_EINVAL, "the solve needs %zu bytes of workspace, %zu given",
                              src->off, src->cap);
@@ -1390,7 +1395,7 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         if (auto_atom && slot_bytes * P.slots > ctx->ws.bytes) {
             size_t fr = 0, tot = 0;
             if (hipMemGetInfo(&fr, &tot) != hipSuccess || slot_bytes * P.slots > (fr + ctx->ws.bytes) / 2)
-                return without_atom();
+                return plan_again();
         }
         hipError_t grown = hipSuccess;
         const char *what = "";
@@ -1413,10 +1418,10 @@ ma_status make_plan(ma_ctx *ctx, int64_t ncols, const int32_t *cols, int32_t p, 
         grow(ctx->partial, n_partial, "partial");
         grow(ctx->Ecol, n_E, "Ecol");
         grow(ctx->Ncol, n_E, "Ncol");
-        if (grown != hipSuccess && auto_atom) {
+        if (grown != hipSuccess && another) {
             ctx->ws.release();
             ctx->mid.release();
-            return without_atom();
+            return plan_again();
         }
         HIPCHK(ctx, grown, what);
         b_lists = ctx->lists.p;

@@ -150,3 +150,24 @@ def test_columns_that_take_the_atom_kernel(env, which, kernel):
                 for x in ({}, dict(basis_kernel="workspace")))
         assert a == b
     ctx.close()
+
+
+def test_dense_operators_without_room_for_the_workspace_kernel(env):
+    """The register form needs no basis workspace: it still runs where a caller's
+    workspace does not hold the workspace kernel's."""
+    torch, ma = env
+    import oracle
+    s = _sp3((4, 4, 4), 100, 4.2)
+    ctx = ma.Context(0)
+    ctx.build_tb(s)
+    p, q = 6, 5
+    buf = torch.empty(_size(ma, ctx, None, p, q, "onchip"), dtype=torch.uint8, device="cuda")
+    assert buf.numel() < _size(ma, ctx, None, p, q, "workspace")
+    ctx.set_workspace(buf)
+    got = _solve(torch, ma, ctx, s, p, q, "auto").reshape(-1, 4, 4)
+    ctx.set_workspace(None)
+    cols = np.arange(8, dtype=np.int32)
+    raw = oracle.solve_raw(s, cols=cols, p=p, q=q)
+    want = oracle.scatter_slots(s, cols, oracle.outputs(s, raw, 0.9, s.kT)[0])
+    assert np.abs(got[:s.blk_ptr[2]] - want[:s.blk_ptr[2]]).max() <= 1e-10
+    ctx.close()
